@@ -470,13 +470,14 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
   // lane) in two more
   enum {
     K_RED, K_IP, K_MRC, K_SUM, K_CAR, K_CRT, K_EE0, NBUCKET = 5, K_RG0 = K_EE0 + NBUCKET, NRG = 3,
-    K_SC0 = K_RG0 + NRG, NSC = 2, NK = K_SC0 + NSC
+    K_SC0 = K_RG0 + NRG, NSC = 2, K_GE0 = K_SC0 + NSC, NK = K_GE0 + GEO_CLASSES
   };
   const int bucket_words[NBUCKET] = {24, 40, 64, 96, 1 << 30};
   const int rg_cap[NRG] = {24, 32, 64};
   int bw[NBUCKET] = {0}, br_[NBUCKET] = {0};
   int rdeg[NRG] = {0}, rw[NRG] = {0};
   int sw[NSC] = {0};
+  int gmax[GEO_CLASSES] = {0};  // interpolation on the geometric nodes: largest D of each class
   std::vector<int> starts[NK];
   for (auto& v : starts) v.assign(nj + 1, 0);
   // the schedule: from the autotuner's table for the batch's size key
@@ -536,6 +537,8 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
       br_[bk] = std::max(br_[bk], x.Tf + x.Tg);
     }
     starts[K_IP][i + 1] = p.P;
+    starts[K_GE0 + geo_class(p.D)][i + 1] = p.P;
+    gmax[geo_class(p.D)] = std::max(gmax[geo_class(p.D)], p.D);
     starts[K_MRC][i + 1] = p.D;  // Garner: one wave per coefficient
     starts[K_SUM][i + 1] = (p.D * x.Lacc + 255) / 256;
     starts[K_CAR][i + 1] = debug ? 0 : (x.degcap + 1 + 63) / 64;
@@ -594,7 +597,14 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
   // the per-(job, prime) interpolation kernel reads its block tables
   const uint32_t *itW = nullptr, *itQ = nullptr;
   int itNB = 0;
-  if (group.empty() && !debug && !noalloc &&
+  // every other batch: the geometric nodes where their tables fit, else the
+  // nodes 0..D-1 with the block tables of the per-(job, prime) kernel
+  TablesDev etab = cx->tab;  // tables of the evaluation and interpolation launches
+  // (the Schur schedule, whose fallback statistics count vanishing pivots at
+  // the points 0..D-1, and the persistent launch keep those nodes)
+  const bool geo = group.empty() && !debug && !noalloc && !fused && !schur && instances > 0 &&
+                   geo_tables_device(cx, maxD, maxP, st, &etab);
+  if (group.empty() && !geo && !debug && !noalloc &&
       !interp_tables_device(cx, interp_table_blocks(maxD), maxP, st, &itW, &itQ, &itNB)) {
     itW = itQ = nullptr;
     itNB = 0;
@@ -766,7 +776,7 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
   }
   const JobDev* d_jobs = (const JobDev*)(D0 + o_jobs);
   int nb_ee = 0;
-  for (int bk = 0; bk < NBUCKET + NRG + NSC; ++bk) nb_ee += nb_of(K_EE0 + bk);
+  for (int bk = 0; bk < NBUCKET + NRG + NSC; ++bk) nb_ee += nb_of(K_EE0 + bk);  // (K_EE0, K_RG0, K_SC0)
 
   // The device sequence of the call: metadata upload, kernels, result copies.
   // seq(run, sig) hashes every argument of every call into sig and, with
@@ -887,7 +897,8 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
     meta_mapped = (const uint32_t*)m;
   }
   auto seq = [&](bool run, SeqHash& sg) -> int {
-    sg.add(st, D0, meta_begin, meta_end, (const void*)meta_mapped);
+    sg.add(st, D0, meta_begin, meta_end, (const void*)meta_mapped, (const void*)etab.qpow, etab.geo_D);
+    for (int c = 0; c < GEO_CLASSES; ++c) sg.add(nb_of(K_GE0 + c), gmax[c]);
     if (run && meta_end > meta_begin) {
       if (noalloc)
         DEV(hipMemcpyAsync(D0 + meta_begin, H0 + meta_begin, meta_end - meta_begin, hipMemcpyHostToDevice, st));
@@ -915,19 +926,19 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
       for (int bk = 0; bk < NBUCKET; ++bk) {
         sg.add(nb_of(K_EE0 + bk), bw[bk], br_[bk]);
         if (run && nb_of(K_EE0 + bk))
-          launch_eval_elim(d_jobs, st_of(K_EE0 + bk), nj, nb_of(K_EE0 + bk), bw[bk], br_[bk], cx->tab, st);
+          launch_eval_elim(d_jobs, st_of(K_EE0 + bk), nj, nb_of(K_EE0 + bk), bw[bk], br_[bk], etab, st);
       }
       for (int r = 0; r < NRG; ++r) {
         sg.add(nb_of(K_RG0 + r), rdeg[r], rw[r], o_fbc, o_fbq[r]);
         if (run && nb_of(K_RG0 + r))
           launch_eval_elim_rg(rg_cap[r], d_jobs, st_of(K_RG0 + r), nj, nb_of(K_RG0 + r), rdeg[r], rw[r],
-                              (int*)(D0 + o_fbc) + r, (int*)(D0 + o_fbq[r]), cx->tab, st);
+                              (int*)(D0 + o_fbc) + r, (int*)(D0 + o_fbq[r]), etab, st);
       }
       for (int r = 0; r < NSC; ++r) {
         sg.add(nb_of(K_SC0 + r), sw[r]);
         if (run && nb_of(K_SC0 + r))
           launch_schur(r + 1, d_jobs, st_of(K_SC0 + r), nj, nb_of(K_SC0 + r), sw[r],
-                       (int*)(D0 + o_flags) + 2 * nj + 2, cx->tab, st);
+                       (int*)(D0 + o_flags) + 2 * nj + 2, etab, st);
       }
       if (run && timing) DEV(hipEventRecord(ev1, st));
       if (!debug) {
@@ -938,7 +949,11 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
           if (!group.empty())
             launch_interp_mfma((uint32_t* const*)(D0 + o_gco), (int)group.size(), gD, gP, vinv,
                                (const int8_t*)(D0 + o_yp), cx->tab, st);
-          else if (nb_of(K_IP))
+          else if (geo) {
+            for (int c = 0; c < GEO_CLASSES; ++c)
+              if (nb_of(K_GE0 + c))
+                launch_interp_geo(c, d_jobs, st_of(K_GE0 + c), nj, nb_of(K_GE0 + c), gmax[c], etab, st);
+          } else if (nb_of(K_IP))
             launch_interp(d_jobs, st_of(K_IP), nj, nb_of(K_IP), maxD, cx->tab, itW, itQ, itNB, st);
           if (use_crt) {
             // residues to limbs in one pass over the output capacity

@@ -232,6 +232,48 @@ bool interp_tables_device(Context* cx, int blocks, int primes, hipStream_t st, c
   return true;
 }
 
+bool geo_tables_device(Context* cx, int D, int P, hipStream_t st, TablesDev* tab) {
+  constexpr size_t kOne = (size_t)512 << 20, kAll = (size_t)1 << 30;
+  std::lock_guard<std::mutex> lk(cx->geo_mu);
+  const Context::GeoTable* hit = nullptr;
+  size_t total = 0;
+  int Dm = (D + 255) & ~255, Pm = std::min((P + 31) & ~31, cx->tab.K);
+  for (const auto& g : cx->geo) {
+    total += g.bytes;
+    if (g.D >= D && g.P >= P && (!hit || g.bytes < hit->bytes)) hit = &g;
+  }
+  if (!hit) {
+    // large enough for the earlier calls too, if that fits, else for this one
+    const int D0 = Dm, P0 = Pm;
+    for (const auto& g : cx->geo) Dm = std::max(Dm, g.D), Pm = std::max(Pm, g.P);
+    if (geo_table_bytes(Dm, Pm) > kOne || total + geo_table_bytes(Dm, Pm) > kAll) Dm = D0, Pm = P0;
+    const size_t bytes = geo_table_bytes(Dm, Pm);
+    if (bytes > kOne || total + bytes > kAll) return false;
+    uint8_t* d = nullptr;
+    if (hipMalloc((void**)&d, bytes) != hipSuccess) {
+      (void)hipGetLastError();
+      return false;
+    }
+    const size_t n = (size_t)Pm * Dm;
+    uint32_t* w = (uint32_t*)d;
+    launch_geo_tables(cx->tab.primes, Dm, Pm, w, w + n, w + 2 * n, (int8_t*)(w + 3 * n), st);
+    if (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess) {
+      (void)hipFree(d);
+      return false;
+    }
+    cx->geo.push_back({d, Dm, Pm, bytes});
+    hit = &cx->geo.back();
+  }
+  const size_t n = (size_t)hit->P * hit->D;
+  const uint32_t* w = (const uint32_t*)hit->p;
+  tab->qpow = w;
+  tab->geo_invu = w + n;
+  tab->geo_w = w + 2 * n;
+  tab->geo_A = (const int8_t*)(w + 3 * n);
+  tab->geo_D = hit->D;
+  return true;
+}
+
 const int8_t* vinv_device(Context* cx, int D, int P, hipStream_t st) {
   constexpr size_t kLimit = (size_t)2 << 30;  // bytes of cached tables
   std::lock_guard<std::mutex> lk(cx->vinv_mu);

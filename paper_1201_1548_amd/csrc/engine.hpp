@@ -109,6 +109,13 @@ struct Context {
   int itab_nb = 0, itab_P = 0;
   size_t itab_qoff = 0;
   std::vector<uint32_t*> itab_retired;                  // outgrown tables (kernels in flight may still read them)
+  struct GeoTable {
+    void* p;
+    int D, P;
+    size_t bytes;
+  };
+  std::mutex geo_mu;                                    // tables of the geometric nodes (geo_tables_device)
+  std::vector<GeoTable> geo;
   std::mutex ev_mu;
   std::vector<hipEvent_t> ev_free;                      // completion events of batched calls, reused
   std::mutex vinv_mu;
@@ -143,6 +150,12 @@ const int8_t* vinv_device(Context* cx, int D, int P, hipStream_t st);
 // blocks itself).  *nb receives the table's block count (its stride).
 bool interp_tables_device(Context* cx, int blocks, int primes, hipStream_t st, const uint32_t** W,
                           const uint32_t** Q, int* nb);
+
+// Fills *tab's tables of the geometric nodes for at least D points and P primes
+// (built on `st`, which is then synchronised, and kept: at most 512 MiB each
+// and 1 GiB in all; never freed, calls in flight may read them).  False when
+// they would not fit or the build failed: the call then uses the nodes 0..D-1.
+bool geo_tables_device(Context* cx, int D, int P, hipStream_t st, TablesDev* tab);
 
 // Device copy of crt_tables(P), built on first use and kept (nullptr on failure).
 const uint32_t* crt_device(Context* cx, int P, int* LM);

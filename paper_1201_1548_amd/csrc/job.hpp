@@ -134,6 +134,14 @@ struct TablesDev {
   const double* inv_p;      // [K]: 1 / p_k rounded to nearest
   int32_t K;
   int32_t dmax;
+  // geometric nodes 2^i (interp_geo.hip), null when a launch uses the nodes
+  // 0..D-1: [P][geo_D] words 2^i, 1 / u_i and u_i 2^(-i(i-1)/2) (Montgomery)
+  // and per prime 64 geo_D bytes of matrix operands
+  const uint32_t* qpow;
+  const uint32_t* geo_invu;
+  const uint32_t* geo_w;
+  const int8_t* geo_A;
+  int32_t geo_D;
 };
 
 }  // namespace bires

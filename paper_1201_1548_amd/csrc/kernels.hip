@@ -29,60 +29,11 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "device.hpp"
 #include "job.hpp"
 #include "kernels.hpp"
 
 namespace bires {
-
-// Block -> job: starts[0..nj] are the first block of each job (starts[nj] =
-// grid size); returns the largest j with starts[j] <= b (uniform, scalar).
-// The job j of block b: starts[j] <= b < starts[j + 1] (nj + 1 prefix
-// entries; jobs without blocks repeat an entry).  With the launch's block
-// count `total`, the guess b nj / total is the answer whenever the jobs have
-// equal block counts, and two independent loads confirm it; otherwise (or
-// with total = 0) a binary search, whose dependent loads cost a round trip
-// to L2 each.
-__device__ __forceinline__ int find_job(const int* __restrict__ starts, int nj, int b, int total = 0) {
-  if (total > 0) {
-    const int g = min((int)(((unsigned long long)b * (unsigned)nj) / (unsigned)total), nj - 1);
-    if (starts[g] <= b && b < starts[g + 1]) return g;
-  }
-  int lo = 0, hi = nj;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (starts[mid] <= b) lo = mid;
-    else hi = mid;
-  }
-  return lo;
-}
-
-// Global-memory view of a pointer the host guarantees to be device memory:
-// loads through it compile to global (not flat) loads, which do not share
-// the LDS wait counter.
-template <class T>
-__device__ __forceinline__ const __attribute__((address_space(1))) T* gmem(const T* p) {
-  return (const __attribute__((address_space(1))) T*)p;
-}
-
-// Lane of the calling thread in its wave.  The device functions that one wave
-// runs index with it, so that a block of several waves (the persistent
-// launch) can give each wave a task of its own.
-__device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & 63u); }
-
-// Synchronisation of the threads that run a device function together: the
-// whole block, or (WAVE) one wave of it.  A wave's LDS accesses complete in
-// order, so the wave needs no barrier; the fences keep the compiler from
-// moving memory accesses across the point.
-template <bool WAVE>
-__device__ __forceinline__ void group_sync() {
-  if constexpr (WAVE) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  } else {
-    __syncthreads();
-  }
-}
 
 // ---------------------------------------------------------------------------
 // planning statistics: for each row j of a rectangle, the x-degree, the
@@ -433,32 +384,6 @@ __device__ uint32_t uni_resultant(uint32_t* A, uint32_t* B, int m, int n, const 
   return neg ? mneg(r, q.p) : r;
 }
 
-// a b + c with 32-bit a, b (one v_mad_u64_u32).  Inline assembly keeps a as a
-// single 32-bit register where the compiler would keep a zero-extended pair.
-// SB: b is wave-uniform and held in a scalar register (the residues read
-// through the scalar cache).
-template <bool SB = false>
-__device__ __forceinline__ uint64_t mad_u64_u32(uint32_t a, uint32_t b, uint64_t c) {
-  uint64_t d;
-  uint64_t carry;
-  if constexpr (SB)
-    asm("v_mad_u64_u32 %0, %1, %2, %3, %4" : "=v"(d), "=s"(carry) : "v"(a), "s"(b), "v"(c));
-  else
-    asm("v_mad_u64_u32 %0, %1, %2, %3, %4" : "=v"(d), "=s"(carry) : "v"(a), "v"(b), "v"(c));
-  return d;
-}
-
-// Exact sums of products of residues in 96 bits: 64-bit partial sums (up to
-// eight products of residues, below 8 p^2 < 2^64) added with a carry word.
-struct Acc96 {
-  uint64_t lo = 0;
-  uint32_t hi = 0;
-  __device__ void add(uint64_t s) {
-    lo += s;
-    hi += lo < s ? 1u : 0u;
-  }
-};
-
 // (b) evaluation at x = a.  With Montgomery residues c_M of a row and the
 // Montgomery powers (a^i)_M, S = sum_i c_M (a^i)_M is f_j(a) R^2 mod p; S is
 // summed exactly and one reduction turns it into f_j(a) R.  The powers live
@@ -485,16 +410,6 @@ __device__ __forceinline__ size_t im_off(int row, int idx, int Kp) {
   return ((((size_t)rt * (Kp >> 5) + ks) * 64) + r + 32 * g) * 16 + b;
 }
 
-// The four balanced base-256 digits of the symmetric representative v of
-// x mod p, packed little-endian into one word.  Adding 128 at each of the
-// three low digit positions makes those digits d_s + 128 in [0, 255] (plain
-// base 256), with the top digit (|d_3| <= 64) left in the top byte; flipping
-// bit 7 of the three low bytes subtracts the 128 again in int8 terms.
-__device__ __forceinline__ uint32_t digits4(uint32_t x, uint32_t p) {
-  const uint32_t v = x > (p >> 1) ? x - p : x;
-  return (v + 0x808080u) ^ 0x808080u;
-}
-
 // The value v = R(a) mod p_k (plain residue) of point a of job J: into vals,
 // or for a job of the matrix-core interpolation group straight into the
 // group's four digit planes of prime k (column ycol), which the
@@ -519,7 +434,6 @@ __device__ __forceinline__ void put_value(const JobDev& J, int k, int a, uint32_
 }
 
 // Read-only data with wave-uniform addresses, read through the scalar cache.
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(4))) const uint32_t cu32;
 typedef __attribute__((address_space(4))) const u32x4 cu4;
 typedef __attribute__((address_space(4))) const int32_t ci32;
@@ -582,10 +496,11 @@ __device__ __forceinline__ uint32_t eval_row(C* c, int d, const uint32_t (&pw)[N
 // scalar cache, which is valid when the residues were written by an earlier
 // launch (the staged schedule); the persistent fused launch, which writes
 // them itself, uses ordinary loads.
-// f(a, y) and g(a, y) modulo p_k (Montgomery form) at the point a = pt into
-// the lane arrays A[j W], B[j W] (ascending powers of y).
+// f(a, y) and g(a, y) modulo p_k (Montgomery form) at the point a (Montgomery
+// form aM) into the lane arrays A[j W], B[j W] (ascending powers of y).
 template <int W, bool SC>
-__device__ __forceinline__ void eval_pair(const JobDev& J, int k, int pt, const ModP& q, uint32_t* A, uint32_t* B) {
+__device__ __forceinline__ void eval_pair(const JobDev& J, int k, uint32_t aM, const ModP& q, uint32_t* A,
+                                          uint32_t* B) {
   typedef typename std::conditional<SC, cu32, const uint32_t>::type RW;
   typedef typename std::conditional<SC, cu4, const u32x4>::type RW4;
   typedef typename std::conditional<SC, ci32, const int32_t>::type RI;
@@ -595,7 +510,6 @@ __device__ __forceinline__ void eval_pair(const JobDev& J, int k, int pt, const 
   RW* Rg = (RW*)(J.res_g + (size_t)k * J.Tg);
   RI* RDf = (RI*)J.rowdeg_f;
   RI* RDg = (RI*)J.rowdeg_g;
-  const uint32_t aM = to_mont((uint32_t)pt, q);
   const int dmax = max(J.ldf, J.kind ? J.ldf : J.ldg) - 1;
   uint32_t pw[EV_PW];
   pw[0] = q.one;
@@ -619,19 +533,9 @@ __device__ __forceinline__ void dev_eval_elim(const JobDev& J, int lb, TablesDev
   const int pt = a0 + lane_id();
   if (pt >= J.D) return;
   const ModP q = tab.primes[k];
-  eval_pair<W, SC>(J, k, pt, q, A, B);
+  eval_pair<W, SC>(J, k, eval_point(tab, k, pt, q), q, A, B);
   const uint32_t r = uni_resultant<W>(A, B, m, n, q);
   put_value(J, k, pt, from_mont(r, q), q.p);
-}
-
-// Workgroups are dispatched to the 8 XCDs round-robin in blockIdx order, and
-// each XCD has its own L2.  This bijection of [0, nb) gives XCD x the
-// contiguous logical range [x q + min(x, r), ...) of q + (x < r) blocks
-// (q = nb / 8, r = nb % 8), so the blocks of one (job, prime), which share
-// that prime's residues, run on one XCD and share its L2.
-__device__ __forceinline__ int xcd_block(int b, int nb) {
-  const int q = nb >> 3, r = nb & 7, x = b & 7;
-  return x * q + min(x, r) + (b >> 3);
 }
 
 template <int W>
@@ -830,7 +734,7 @@ __device__ __forceinline__ bool dev_eval_elim_rg(const JobDev& J, int lb, Tables
   const int pt = a0 + lane_id();
   if (pt >= J.D) return true;
   const ModP q = tab.primes[k];
-  const uint32_t aM = to_mont((uint32_t)pt, q);
+  const uint32_t aM = eval_point(tab, k, pt, q);
   const int dmax = max(J.ldf, J.kind ? J.ldf : J.ldg) - 1;
   uint32_t pw[RG_PW];
   pw[0] = q.one;
@@ -1003,7 +907,7 @@ __global__ __launch_bounds__(64) void k_schur(const JobDev* jobs, const int* sta
   const ModP q = tab.primes[k];
   const uint32_t* Rf = J.res_f + (size_t)k * J.Tf;
   const uint32_t* Rg = J.res_g + (size_t)k * J.Tg;
-  const uint32_t aM = to_mont((uint32_t)pt, q);
+  const uint32_t aM = eval_point(tab, k, pt, q);
   const int dmax = max(J.ldf, J.kind ? J.ldf : J.ldg) - 1;
   uint32_t pw[EV_PW];
   pw[0] = q.one;
@@ -1208,7 +1112,7 @@ __global__ __launch_bounds__(W) void k_psc(JobDev J, TablesDev tab, PscOut o) {
   uint32_t* A = lds + threadIdx.x;
   uint32_t* B = A + (J.m + 1) * W;
   const ModP q = tab.primes[0];
-  eval_pair<W, true>(J, 0, pt, q, A, B);
+  eval_pair<W, true>(J, 0, eval_point(tab, 0, pt, q), q, A, B);
   psc_lane<W>(A, B, J.m, J.n, pt, J.D, q, o);
 }
 
@@ -1488,9 +1392,6 @@ size_t interp_lds_words(int D) { return (size_t)3 * D + 144 + (size_t)((D + KB -
 // row tile rt (32 rows) and contraction step ks (32 indices) one 1 KiB block
 // holds lane L = r + 32 g's 16 bytes (row 32 rt + r, indices 32 ks + 16 g +
 // 0..15), so each operand load of a wave reads 1 KiB contiguously.
-
-typedef int im_v4i __attribute__((ext_vector_type(4)));
-typedef int im_v16i __attribute__((ext_vector_type(16)));
 
 __device__ __forceinline__ void put_digits(int8_t* base, size_t plane, size_t off, uint32_t d) {
 #pragma unroll

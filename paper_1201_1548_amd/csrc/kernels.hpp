@@ -70,6 +70,17 @@ int interp_table_blocks(int max_points);
 size_t interp_table_words(int blocks, int primes, size_t* q_offset);
 void launch_interp_tables(int blocks, int primes, TablesDev tab, uint32_t* W, uint32_t* Q, hipStream_t s);
 size_t interp_lds_words(int D);
+// Interpolation on the geometric nodes 2^i (interp_geo.hip): the tables of P
+// primes for Dc indices (a multiple of 256; geo_table_bytes in all), and one
+// block per (job, prime) of the jobs of one class (geo_class of D); the jobs'
+// values are those at the nodes tab.qpow and tab.geo_D covers max_points.
+size_t geo_table_bytes(int Dc, int P);
+void launch_geo_tables(const ModP* primes, int Dc, int P, uint32_t* qpow, uint32_t* invu, uint32_t* wt, int8_t* A,
+                       hipStream_t s);
+constexpr int GEO_CLASSES = 4;
+int geo_class(int D);
+void launch_interp_geo(int cls, const JobDev* jobs, const int* starts, int nj, int nblocks, int max_points,
+                       TablesDev tab, hipStream_t s);
 // Interpolation of N jobs sharing D and P (gco[n] the coefs of job n of the
 // group) as int8 matrix-core products with V^{-1}: Ap = vinv_bytes(Dp, P)
 // bytes built by launch_vinv (Dp = D rounded up to 32); Yp = 4 Np Dp P bytes

@@ -3,9 +3,10 @@
 // "Computation of N^-").
 //
 // psc: the inputs are reduced modulo the prime (k_reduce), every point
-// a = 0..D-1 runs the subresultant recurrence in one lane (k_psc), and each
-// index i is interpolated on the nodes 0..D-1 (k_interp, one block per
-// index).  D is the resultant's point count: sr_i is a minor of the Sylvester
+// of the D nodes runs the subresultant recurrence in one lane (k_psc), and
+// each index i is interpolated on those nodes (k_interp_geo on the nodes 2^a,
+// or k_interp on 0..D-1 where the tables of the former would not fit; one
+// block per index).  D is the resultant's point count: sr_i is a minor of the Sylvester
 // matrix's rows (n - i rows of f, m - i of g), so the degree bound of R bounds
 // it too.  The prime must be one of the library's table primes (the largest
 // below 2^32 / 3), whose tables the kernels index; the kernels see the table
@@ -80,6 +81,13 @@ TablesDev shifted(const TablesDev& t, int k) {
   s.invfact += (size_t)k * t.dmax;
   s.inv_p += k;
   s.K -= k;
+  if (s.qpow) {
+    const size_t o = (size_t)k * t.geo_D;
+    s.qpow += o;
+    s.geo_invu += o;
+    s.geo_w += o;
+    s.geo_A += 64 * o;
+  }
   return s;
 }
 
@@ -175,11 +183,16 @@ static int psc_device(Context* cx, const HostJob& h, int kind, int kp, int kmax,
     is[i] = i;
   }
   is[K] = K;
-  const TablesDev tab = shifted(cx->tab, kp);
+  TablesDev base = cx->tab;
+  const bool geo = geo_tables_device(cx, D, kp + 1, st, &base);
+  const TablesDev tab = shifted(base, kp);
   DEV(hipMemcpyAsync(r.ws.p, H, up_end, hipMemcpyHostToDevice, st));
   launch_reduce(r.ws.as<JobDev>(o_job), r.ws.as<int>(o_st), 1, st2[1], 1, tab, st);
   launch_psc(J, tab, r.ws.as<uint32_t>(o_num), r.ws.as<uint32_t>(o_den), K, st);
-  launch_interp(r.ws.as<JobDev>(o_ij), r.ws.as<int>(o_is), K, K, D, tab, nullptr, nullptr, 0, st);
+  if (geo)
+    launch_interp_geo(geo_class(D), r.ws.as<JobDev>(o_ij), r.ws.as<int>(o_is), K, K, D, tab, st);
+  else
+    launch_interp(r.ws.as<JobDev>(o_ij), r.ws.as<int>(o_is), K, K, D, tab, nullptr, nullptr, 0, st);
   DEV(hipGetLastError());
   // the staging block is read by the copy: it must outlive it
   DEV(hipStreamSynchronize(st));
