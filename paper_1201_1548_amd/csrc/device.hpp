@@ -83,6 +83,14 @@ struct Acc96 {
   }
 };
 
+// S R^{-1} mod p for S = hi 2^64 + lo with hi < 2^32 - 4 (here hi <= 2):
+// REDC(lo_lo + hi R^2) = lo_lo R^{-1} + hi R, and lo_hi R R^{-1} = lo_hi.
+// The REDC argument is below p 2^32, so its result is below 2p.
+__device__ __forceinline__ uint32_t fold96(const Acc96& S, const ModP& q) {
+  const uint64_t t = (uint64_t)S.hi * q.r2 + (uint32_t)S.lo;
+  return madd(redc(t, q.p, q.pinv), reduce32((uint32_t)(S.lo >> 32), q.p), q.p);
+}
+
 // The four balanced base-256 digits of the symmetric representative v of
 // x mod p, packed little-endian into one word.  Adding 128 at each of the
 // three low digit positions makes those digits d_s + 128 in [0, 255] (plain

@@ -393,14 +393,6 @@ __device__ uint32_t uni_resultant(uint32_t* A, uint32_t* B, int m, int n, const 
 // of EV_PW, combined by Horner's rule in a^EV_PW.
 constexpr int EV_PW = 24;
 
-// S R^{-1} mod p for S = hi 2^64 + lo with hi < 2^32 - 4 (here hi <= 2):
-// REDC(lo_lo + hi R^2) = lo_lo R^{-1} + hi R, and lo_hi R R^{-1} = lo_hi.
-// The REDC argument is below p 2^32, so its result is below 2p.
-__device__ __forceinline__ uint32_t fold96(const Acc96& S, const ModP& q) {
-  const uint64_t t = (uint64_t)S.hi * q.r2 + (uint32_t)S.lo;
-  return madd(redc(t, q.p, q.pinv), reduce32((uint32_t)(S.lo >> 32), q.p), q.p);
-}
-
 // Byte offset of element (row, idx) of a digit plane of the matrix-core
 // interpolation with Kp = padded contraction length, in operand order: 1 KiB
 // blocks per (32-row tile, 32-wide step), lane l of an operand holding row
@@ -2560,238 +2552,6 @@ void launch_fused(int C, int KS, const FusedPlan& F, size_t lds_bytes, int block
 }
 
 // ---------------------------------------------------------------------------
-// (a8) modular gcd per prime (Section 5.1, "Computing gcds in Z[x]", step (b)).
-// One block per prime: Euclid's algorithm over F_p on a, b without inverses
-// (each elimination A <- lc(B) A - lc(A) y^s B changes A only by a unit
-// factor, so the last non-zero remainder is the gcd up to a unit); the result
-// is made monic with one inverse.  Then waves 0 and 1 divide a and b exactly
-// by the monic gcd (synthetic division, sequential over the quotient).
-// Outputs are scaled for the integer reconstruction: beta g, (lc a / beta) a/g,
-// (lc b / beta) b/g, whose images multiply to lc(a) a and lc(b) b.
-
-// Euclid's algorithm over F_p on X (degree a) and Y (degree b) in LDS, run by
-// the whole block, without inverses: each elimination X <- lc(Y) X - lc(X)
-// y^s Y changes X only by a unit factor, so the last non-zero remainder is an
-// associate of the gcd.  Leading coefficients must be non-zero.  Returns the
-// gcd's degree d, with an associate of the gcd in Y[0..d] (the pointers are
-// swapped as the roles alternate; both arrays need max(a, b) + 1 words).
-__device__ int block_gcd_fp(uint32_t*& X, uint32_t*& Y, int a, int b, const ModP& q) {
-  const int tid = threadIdx.x;
-  if (a < b) {
-    uint32_t* T = X; X = Y; Y = T;
-    int t = a; a = b; b = t;
-  }
-  int d = 0;
-  for (;;) {
-    if (b == 0) {  // a non-zero constant divides both
-      d = 0;
-      break;
-    }
-    const uint32_t lb = Y[b];
-    if (a == b + 1) {
-      // the usual step: both eliminations in one pass, as in eliminate()
-      // (X_t <- lb^2 X_t - lb X_a Y_{t-1} - X'_{a-1} Y_t with X'_{a-1} the
-      // first elimination's new top coefficient)
-      const uint32_t nla = mneg(X[a], q.p);
-      const uint32_t n2 = mneg(mdot2(lb, X[a - 1], nla, Y[b - 1], q), q.p);
-      const uint32_t l2 = mmul(lb, lb, q), l1 = mmul(lb, nla, q);
-      __syncthreads();  // every thread has read X[a], X[a-1] before they can be overwritten below
-      for (int t = tid; t < b; t += blockDim.x)
-        X[t] = t ? mdot3(l2, X[t], l1, Y[t - 1], n2, Y[t], q) : mdot2(l2, X[0], n2, Y[0], q);
-      __syncthreads();
-    } else {
-      for (int aa = a; aa >= b; --aa) {
-        const uint32_t nla = mneg(X[aa], q.p);
-        const int s = aa - b;
-        __syncthreads();  // every thread has read X[aa] before it can be overwritten below
-        for (int t = tid; t < aa; t += blockDim.x)
-          X[t] = t < s ? mmul(lb, X[t], q) : mdot2(lb, X[t], nla, Y[t - s], q);
-        __syncthreads();
-      }
-    }
-    int c = b - 1;
-    while (c >= 0 && X[c] == 0u) --c;
-    if (c < 0) {
-      d = b;
-      break;
-    }
-    uint32_t* T = X; X = Y; Y = T;
-    a = b;
-    b = c;
-  }
-  return d;
-}
-
-__global__ __launch_bounds__(256) void k_gcd_p(GcdDev G, TablesDev tab) {
-  extern __shared__ __align__(16) uint32_t lds[];
-  const int k = blockIdx.x;
-  const ModP q = tab.primes[k];
-  const int da = G.da, db = G.db;
-  const int mx = da > db ? da : db;
-  const int mn = da < db ? da : db;
-  uint32_t* A0 = lds;
-  uint32_t* B0 = A0 + da + 1;
-  uint32_t* X = B0 + db + 1;
-  uint32_t* Y = X + mx + 1;
-  uint32_t* Gm = Y + mx + 1;
-  const int tid = threadIdx.x;
-  const uint32_t* ra = G.res_a + (size_t)k * (da + 1);
-  const uint32_t* rb = G.res_b + (size_t)k * (db + 1);
-  for (int i = tid; i <= da; i += blockDim.x) A0[i] = X[i] = ra[i];
-  for (int i = tid; i <= db; i += blockDim.x) B0[i] = Y[i] = rb[i];
-  __syncthreads();
-  if (A0[da] == 0u || B0[db] == 0u) {
-    if (tid == 0) G.gdeg[k] = -2;
-    return;
-  }
-  const int d = block_gcd_fp(X, Y, da, db, q);
-  // monic gcd (Montgomery) in Gm; b == 0 means gcd 1
-  const uint32_t inv = d ? minv(Y[d], q) : q.one;
-  for (int i = tid; i <= d; i += blockDim.x) Gm[i] = d ? mmul(Y[i], inv, q) : q.one;
-  __syncthreads();
-  const uint32_t beta = G.sc[3 * k], sa = G.sc[3 * k + 1], sb = G.sc[3 * k + 2];
-  uint32_t* F = G.F + (size_t)k * (mn + 1);
-  for (int i = tid; i <= mn; i += blockDim.x) F[i] = i <= d ? mmul(Gm[i], beta, q) : 0u;
-  // cofactors: wave 0 divides a, wave 1 divides b (in X and Y as work arrays)
-  const int wave = tid >> 6, lane = tid & 63;
-  __shared__ int bad_any;
-  if (tid == 0) bad_any = 0;
-  __syncthreads();
-  if (wave < 2) {
-    const int dn = wave ? db : da;
-    const uint32_t* src = wave ? B0 : A0;
-    uint32_t* W = wave ? Y : X;
-    uint32_t* out = wave ? G.QB + (size_t)k * (db + 1) : G.QA + (size_t)k * (da + 1);
-    const uint32_t scl = wave ? sb : sa;
-    for (int i = lane; i <= dn; i += 64) W[i] = src[i];
-    bool bad = false;
-    for (int kq = dn - d; kq >= 0; --kq) {
-      const uint32_t qc = W[kq + d];
-      for (int i = lane; i < d; i += 64) W[kq + i] = msub(W[kq + i], mmul(qc, Gm[i], q), q.p);
-      if (lane == 0) out[kq] = mmul(qc, scl, q);
-    }
-    for (int i = lane; i < d; i += 64) bad |= W[i] != 0u;
-    for (int i = dn - d + 1 + lane; i <= dn; i += 64) out[i] = 0u;
-    if (__ballot(bad) != 0ull && lane == 0) atomicOr(&bad_any, 1);
-  }
-  __syncthreads();
-  if (tid == 0) G.gdeg[k] = bad_any ? -3 : d;
-}
-
-// ---------------------------------------------------------------------------
-// The degree chain of the N^- / N^+ test (Section 3.2.2) over F_p, one block:
-//   S_0 = R* mod p, S_i = gcd(S_{i-1}, sr_i) (i >= 1, until S_i is constant),
-//   and deg gcd(R^inf, Q) = the degrees of the gcds removed from Q by
-//   H <- H / gcd(H, R*) until that gcd is constant.
-// Inputs in Montgomery form or plain as stated; every gcd is block_gcd_fp.
-
-// Degree of v[0..n) (-1 for zero), computed by the block.
-__device__ int block_degree(const uint32_t* v, int n, int* red) {
-  int top = -1;
-  for (int i = threadIdx.x; i < n; i += blockDim.x)
-    if (v[i] != 0u) top = i;
-  __syncthreads();
-  if (threadIdx.x == 0) *red = -1;
-  __syncthreads();
-  if (top >= 0) atomicMax(red, top);
-  __syncthreads();
-  const int d = *red;
-  __syncthreads();
-  return d;
-}
-
-__global__ __launch_bounds__(256) void k_fiber_chain(ChainDev C, TablesDev tab) {
-  extern __shared__ __align__(16) uint32_t lds[];
-  __shared__ int red;
-  const ModP q = tab.primes[0];
-  const int tid = threadIdx.x;
-  const int mx = max(max(C.dr + 1, C.D), C.Dq);
-  uint32_t* S = lds;            // current S_i, then R* for the common part
-  uint32_t* X = S + mx;
-  uint32_t* Y = X + mx;
-  uint32_t* H = Y + mx;         // Q / (removed gcds)
-  for (int i = tid; i < mx; i += blockDim.x) S[i] = i <= C.dr ? C.rstar[i] : 0u;
-  int ds = block_degree(S, C.dr + 1, &red);
-  const int d0 = ds;
-  if (tid == 0) C.out[0] = ds;
-  int i = 1;
-  for (; i < C.K && ds >= 1; ++i) {
-    const uint32_t* sr = C.srs + (size_t)i * C.D;
-    for (int t = tid; t < C.D; t += blockDim.x) Y[t] = to_mont(sr[t], q);
-    const int db = block_degree(Y, C.D, &red);
-    if (db >= 0) {  // gcd(S, 0) = S
-      for (int t = tid; t <= ds; t += blockDim.x) X[t] = S[t];
-      __syncthreads();
-      uint32_t* Xp = X;
-      uint32_t* Yp = Y;
-      const int d = block_gcd_fp(Xp, Yp, ds, db, q);
-      __syncthreads();
-      for (int t = tid; t <= d; t += blockDim.x) S[t] = Yp[t];
-      ds = d;
-      __syncthreads();
-    }
-    if (tid == 0) C.out[i] = ds;
-  }
-  for (; i < C.K; ++i)
-    if (tid == 0) C.out[i] = 0;
-  // the common part of R and Q with Q's multiplicities
-  for (int t = tid; t < mx; t += blockDim.x) {
-    S[t] = t <= C.dr ? C.rstar[t] : 0u;
-    H[t] = t < C.Dq ? to_mont(C.qpol[t], q) : 0u;
-  }
-  int dh = block_degree(H, C.Dq, &red);
-  int total = 0;
-  while (dh >= 1 && d0 >= 1) {
-    for (int t = tid; t <= dh; t += blockDim.x) X[t] = H[t];
-    for (int t = tid; t <= d0; t += blockDim.x) Y[t] = S[t];
-    __syncthreads();
-    uint32_t* Xp = X;
-    uint32_t* Yp = Y;
-    const int d = block_gcd_fp(Xp, Yp, dh, d0, q);
-    __syncthreads();
-    if (d == 0) break;
-    total += d;
-    // H <- H / G (G = Yp[0..d], made monic), wave 0 by synthetic division
-    const uint32_t inv = minv(Yp[d], q);
-    for (int t = tid; t <= d; t += blockDim.x) Yp[t] = mmul(Yp[t], inv, q);
-    __syncthreads();
-    if (tid < 64) {
-      for (int kq = dh - d; kq >= 0; --kq) {
-        const uint32_t qc = H[kq + d];
-        for (int t = tid; t < d; t += 64) H[kq + t] = msub(H[kq + t], mmul(qc, Yp[t], q), q.p);
-        if (tid == 0) Xp[kq] = qc;  // the quotient (Xp is free again)
-      }
-    }
-    __syncthreads();
-    dh -= d;
-    for (int t = tid; t < mx; t += blockDim.x) H[t] = t <= dh ? Xp[t] : 0u;
-    __syncthreads();
-  }
-  if (tid == 0) {
-    C.out[C.K] = total;
-    C.out[C.K + 1] = dh < 0 ? 1 : 0;
-  }
-}
-
-size_t fiber_chain_lds_bytes(int dr, int D, int Dq) {
-  int mx = dr + 1 > D ? dr + 1 : D;
-  if (Dq > mx) mx = Dq;
-  return (size_t)4 * mx * sizeof(uint32_t);
-}
-
-void launch_fiber_chain(const ChainDev& C, TablesDev tab, hipStream_t s) {
-  hipLaunchKernelGGL(k_fiber_chain, dim3(1), dim3(256), fiber_chain_lds_bytes(C.dr, C.D, C.Dq), s, C, tab);
-}
-
-size_t gcd_lds_bytes(int da, int db) {
-  const int mx = da > db ? da : db, mn = da < db ? da : db;
-  return (size_t)(da + db + 2 + 2 * (mx + 1) + mn + 1) * sizeof(uint32_t);
-}
-
-void launch_gcd_p(const GcdDev& g, TablesDev tab, hipStream_t s) {
-  hipLaunchKernelGGL(k_gcd_p, dim3(g.P), dim3(256), gcd_lds_bytes(g.da, g.db), s, g, tab);
-}
-
 // dst[r][0..n) = src[idx[r]][0..n) (row stride of src: ld words)
 __global__ void k_gather_rows(const uint32_t* src, int ld, const int* idx, int rows, int n, uint32_t* dst) {
   const int r = blockIdx.y;

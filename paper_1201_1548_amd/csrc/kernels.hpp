@@ -127,9 +127,10 @@ void launch_fused(int C, int KS, const FusedPlan& F, size_t lds_bytes, int block
 // den ([K][D]) as workspace.
 size_t psc_lds_bytes(int m, int n);
 void launch_psc(const JobDev& J, TablesDev tab, uint32_t* num, uint32_t* den, int K, hipStream_t s);
-// The N^- / N^+ degree chain over prime index 0 of tab, one block.
+// The N^- / N^+ degree chain over prime index 0 of tab, two blocks (the second
+// buffers of the gcds only where lds_per_block has room for them).
 size_t fiber_chain_lds_bytes(int dr, int D, int Dq);
-void launch_fiber_chain(const ChainDev& C, TablesDev tab, hipStream_t s);
+void launch_fiber_chain(const ChainDev& C, size_t lds_per_block, TablesDev tab, hipStream_t s);
 size_t gcd_lds_bytes(int da, int db);
 void launch_gcd_p(const GcdDev& g, TablesDev tab, hipStream_t s);
 void launch_gather_rows(const uint32_t* src, int ld, const int* idx, int rows, int n, uint32_t* dst, hipStream_t s);

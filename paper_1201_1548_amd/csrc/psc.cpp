@@ -13,7 +13,7 @@
 // shifted so that the prime is index 0.
 //
 // Fiber bounds: with the psc's of (f, f_y) and Q = res(f_x, f_y; y) modulo p
-// on the device, one block (k_fiber_chain) runs the gcd chain S_i and the
+// on the device, one launch (k_fiber_chain) runs the gcd chain S_i and the
 // common part of R* and Q over F_p.  The host adds up
 //   N^- = sum_{i >= 1} (n_y - i) (deg S_{i-1} - deg S_i)      (eq. lower-bound),
 //   N^+ = deg R* n_y - deg R + deg gcd(R^inf mod p, Q mod p)   (eq. up-bound).
@@ -321,7 +321,7 @@ int run_fiber_bounds(Context* cx, const bires_bipoly& f, int var, const bires_up
   const TablesDev tab = shifted(cx->tab, kp);
   DEV(hipMemcpyAsync(ws.p, H, up_end, hipMemcpyHostToDevice, st));
   launch_reduce(ws.as<JobDev>(o_job), ws.as<int>(o_st), 1, st2[1], 1, tab, st);
-  launch_fiber_chain(C, tab, st);
+  launch_fiber_chain(C, cx->lds_per_block, tab, st);
   DEV(hipGetLastError());
   std::vector<int32_t> out(rd.K + 2);
   DEV(hipMemcpyAsync(out.data(), C.out, out.size() * 4, hipMemcpyDeviceToHost, st));
