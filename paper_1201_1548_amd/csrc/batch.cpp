@@ -469,7 +469,7 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
   // jobs on the Schur kernel (wave per instance; 1 or 2 generator rows per
   // lane) in two more
   enum {
-    K_RED, K_IP, K_MRC, K_SUM, K_CAR, K_CRT, K_EE0, NBUCKET = 5, K_RG0 = K_EE0 + NBUCKET, NRG = 3,
+    K_RED, K_IP, K_MRC, K_SUM, K_CAR, K_CRT0, K_EE0 = K_CRT0 + CRT_CLASSES, NBUCKET = 5, K_RG0 = K_EE0 + NBUCKET, NRG = 3,
     K_SC0 = K_RG0 + NRG, NSC = 2, K_GE0 = K_SC0 + NSC, NK = K_GE0 + GEO_CLASSES
   };
   const int bucket_words[NBUCKET] = {24, 40, 64, 96, 1 << 30};
@@ -539,43 +539,83 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
     starts[K_IP][i + 1] = p.P;
     starts[K_GE0 + geo_class(p.D)][i + 1] = p.P;
     gmax[geo_class(p.D)] = std::max(gmax[geo_class(p.D)], p.D);
-    starts[K_MRC][i + 1] = p.D;  // Garner: one wave per coefficient
-    starts[K_SUM][i + 1] = (p.D * x.Lacc + 255) / 256;
-    starts[K_CAR][i + 1] = debug ? 0 : (x.degcap + 1 + 63) / 64;
-    // coefficients below D (the blocks also write the zero ones above them);
-    // divided below by the rows per block, which depend on the largest prime
-    // count
-    starts[K_CRT][i + 1] = debug ? 0 : std::min(p.D, x.degcap + 1);
-  }
-  {
-    const int rows = crt_rows_per_block(maxP);
-    for (int i = 0; i < nj; ++i) starts[K_CRT][i + 1] = (starts[K_CRT][i + 1] + rows - 1) / rows;
   }
   int maxLcap = 1;
   for (int i = 0; i < nj; ++i)
     if (!w[i].status && w[i].active) maxLcap = std::max(maxLcap, w[i].Lout);
+  const bool fused = P->fused = sched == BIRES_SCHEDULE_FUSED;
+  // Reconstruction: the explicit CRT straight to limbs by class of prime count
+  // (crt_class; the operand tables are per prime count), Garner's digits for
+  // the jobs without tables or whose operands do not fit in LDS.  The
+  // persistent launch runs all jobs one way, the CRT up to CRT_SMALL_PRIMES.
+  std::vector<std::pair<const uint32_t*, int>> crt(nj, {nullptr, 0});
+  bool use_crt = fused && !debug && maxP <= CRT_SMALL_PRIMES;  // the persistent launch's choice
+  int crtP[CRT_CLASSES] = {0}, crtL[CRT_CLASSES] = {0};         // largest prime count, limb capacity per class
+  size_t crt_lds[CRT_CLASSES] = {0};
+  {
+    int lastP = -1, lastLM = 0;
+    const uint32_t* lastd = nullptr;
+    std::vector<int> cls(nj, -1);
+    long long small_blocks = 0;
+    int small_top = -1;
+    for (int i = 0; i < nj && !debug && (!fused || use_crt); ++i) {
+      const Work& x = w[i];
+      if (x.status || !x.active) continue;
+      const int Pi = x.pl.P, c = crt_class(Pi);
+      if (c < 0) continue;
+      if (Pi != lastP) {  // consecutive jobs mostly share P
+        lastP = Pi;
+        // allocation-free calls use only operand tables that already exist
+        lastd = noalloc ? crt_device_cached(cx, lastP, &lastLM) : crt_device(cx, lastP, st, &lastLM);
+      }
+      if (!lastd) {
+        use_crt = false;
+        continue;
+      }
+      if (c == CRT_BIG && (crt_big_lds_bytes(Pi, lastLM) > cx->lds_per_block || !crt_big_limbs_ok(lastLM, x.Lout)))
+        continue;
+      crt[i] = {lastd, lastLM};
+      cls[i] = c;
+      if (c != CRT_BIG) {
+        const int rows = crt_rows_per_block(crt_class_primes(c));
+        small_blocks += (std::min(x.pl.D, x.degcap + 1) + rows - 1) / rows;
+        small_top = std::max(small_top, c);
+      }
+    }
+    // few blocks in all: one launch at the largest small class instead of one
+    // per class (a launch costs more than the smaller jobs' unused steps while
+    // every block runs at once, one wave per SIMD)
+    if (small_blocks <= 4ll * cx->compute_units)
+      for (int i = 0; i < nj; ++i)
+        if (cls[i] >= 0 && cls[i] != CRT_BIG) cls[i] = small_top;
+    for (int i = 0; i < nj; ++i)
+      if (cls[i] >= 0) {
+        crtP[cls[i]] = std::max(crtP[cls[i]], w[i].pl.P);
+        crtL[cls[i]] = std::max(crtL[cls[i]], w[i].Lout);
+        if (cls[i] == CRT_BIG) crt_lds[CRT_BIG] = std::max(crt_lds[CRT_BIG], crt_big_lds_bytes(w[i].pl.P, crt[i].second));
+      }
+    for (int c = 0; c < CRT_BIG; ++c)
+      if (crtP[c]) crt_lds[c] = crt_lds_bytes(crtL[c], crtP[c]);
+    if (use_crt && crt_lds_bytes_rows(maxLcap, maxP, 32) > cx->lds_per_block) use_crt = false;
+    for (int i = 0; i < nj; ++i) {
+      const Work& x = w[i];
+      if (x.status || !x.active || debug) continue;
+      // coefficients below D (the CRT's blocks also write the zero ones above)
+      const int rows = std::min(x.pl.D, x.degcap + 1);
+      const int c = cls[i];
+      if (!fused && c >= 0 && crt_lds[c] <= cx->lds_per_block) {
+        const int r = c == CRT_BIG ? 32 : crt_rows_per_block(crtP[c]);
+        starts[K_CRT0 + c][i + 1] = (rows + r - 1) / r;
+      } else if (!use_crt) {
+        starts[K_MRC][i + 1] = x.pl.D;  // Garner: one wave per coefficient
+        starts[K_SUM][i + 1] = (x.pl.D * x.Lacc + 255) / 256;
+        starts[K_CAR][i + 1] = (x.degcap + 1 + 63) / 64;
+      }
+    }
+  }
   for (auto& v : starts)
     for (int i = 0; i < nj; ++i) v[i + 1] += v[i];
-  const bool fused = P->fused = sched == BIRES_SCHEDULE_FUSED;
   if (!fused && !debug) P->schur_instances = (long long)starts[K_SC0][nj] + starts[K_SC0 + 1][nj];
-  // explicit CRT straight to limbs when the prime counts allow
-  std::vector<std::pair<const uint32_t*, int>> crt(nj, {nullptr, 0});
-  bool use_crt = !debug && crt_ok(maxP);
-  int lastP = -1, lastLM = 0;
-  const uint32_t* lastd = nullptr;
-  for (int i = 0; i < nj && use_crt; ++i) {
-    if (w[i].status || !w[i].active) continue;
-    if (w[i].pl.P != lastP) {  // consecutive jobs mostly share P
-      lastP = w[i].pl.P;
-      // allocation-free calls use only operand tables that already exist
-      lastd = noalloc ? crt_device_cached(cx, lastP, &lastLM) : crt_device(cx, lastP, &lastLM);
-    }
-    if (!lastd) use_crt = false;
-    crt[i] = {lastd, lastLM};
-  }
-  // (the fused launch's CRT blocks have 32 rows)
-  if (use_crt && (fused ? crt_lds_bytes_rows(maxLcap, maxP, 32) : crt_lds_bytes(maxLcap, maxP)) > cx->lds_per_block)
-    use_crt = false;
   // interpolation on the matrix cores when at least 32 jobs share D and P
   // (all active jobs of the batch)
   std::vector<int> group;
@@ -944,7 +984,8 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
       if (!debug) {
         sg.add((const void*)itW, (const void*)itQ, itNB);
         sg.add((int)group.size(), gD, gP, (const void*)vinv, o_yp, o_gco, nb_of(K_IP), maxD, use_crt, nb_of(K_CAR),
-               nb_of(K_CRT), maxLcap, nb_of(K_MRC), nb_of(K_SUM));
+               maxLcap, nb_of(K_MRC), nb_of(K_SUM));
+        for (int c = 0; c < CRT_CLASSES; ++c) sg.add(nb_of(K_CRT0 + c), crtP[c], crtL[c], crt_lds[c]);
         if (run) {
           if (!group.empty())
             launch_interp_mfma((uint32_t* const*)(D0 + o_gco), (int)group.size(), gD, gP, vinv,
@@ -955,14 +996,17 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
                 launch_interp_geo(c, d_jobs, st_of(K_GE0 + c), nj, nb_of(K_GE0 + c), gmax[c], etab, st);
           } else if (nb_of(K_IP))
             launch_interp(d_jobs, st_of(K_IP), nj, nb_of(K_IP), maxD, cx->tab, itW, itQ, itNB, st);
-          if (use_crt) {
-            // residues to limbs in one pass over the output capacity
-            if (nb_of(K_CRT)) launch_crt(d_jobs, st_of(K_CRT), nj, nb_of(K_CRT), maxP, maxLcap, cx->tab, st);
-          } else {
-            if (nb_of(K_MRC)) launch_mrc(d_jobs, st_of(K_MRC), nj, nb_of(K_MRC), maxP, cx->tab, st);
-            if (nb_of(K_SUM)) launch_limbs_sum(d_jobs, st_of(K_SUM), nj, nb_of(K_SUM), cx->tab, st);
-            if (nb_of(K_CAR)) launch_limbs_carry(d_jobs, st_of(K_CAR), nj, nb_of(K_CAR), maxLcap, st);
+          // residues to limbs in one pass over the output capacity
+          for (int c = 0; c < CRT_CLASSES; ++c) {
+            if (!nb_of(K_CRT0 + c)) continue;
+            if (c == CRT_BIG)
+              launch_crt_big(d_jobs, st_of(K_CRT0 + c), nj, nb_of(K_CRT0 + c), crt_lds[c], cx->tab, st);
+            else
+              launch_crt(d_jobs, st_of(K_CRT0 + c), nj, nb_of(K_CRT0 + c), crtP[c], crtL[c], cx->tab, st);
           }
+          if (nb_of(K_MRC)) launch_mrc(d_jobs, st_of(K_MRC), nj, nb_of(K_MRC), maxP, cx->tab, st);
+          if (nb_of(K_SUM)) launch_limbs_sum(d_jobs, st_of(K_SUM), nj, nb_of(K_SUM), cx->tab, st);
+          if (nb_of(K_CAR)) launch_limbs_carry(d_jobs, st_of(K_CAR), nj, nb_of(K_CAR), maxLcap, st);
         }
       }
     }

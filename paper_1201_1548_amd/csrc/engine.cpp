@@ -142,22 +142,28 @@ static int init_context(Context& cx) {
   return BIRES_OK;
 }
 
-const uint32_t* crt_device(Context* cx, int P, int* LM) {
+const uint32_t* crt_device(Context* cx, int P, hipStream_t st, int* LM) {
+  constexpr size_t kLimit = (size_t)1 << 30;
   std::lock_guard<std::mutex> lk(cx->crt_mu);
   auto it = cx->crt.find(P);
   if (it == cx->crt.end()) {
-    const CrtHost h = crt_tables(P);
+    const uint32_t* M = &host_tables().pi[(size_t)P * (P + 1) / 2];
+    int lm = P + 1;
+    while (lm > 1 && M[lm - 1] == 0u) --lm;
+    const size_t bytes = crt_table_words(P, lm) * sizeof(uint32_t);
+    if (cx->crt_total + bytes > kLimit) return nullptr;
     uint32_t* d = nullptr;
-    if (hipMalloc(&d, h.buf.size() * sizeof(uint32_t)) != hipSuccess) {
+    if (hipMalloc(&d, bytes) != hipSuccess) {
       (void)hipGetLastError();
       return nullptr;
     }
-    if (hipMemcpy(d, h.buf.data(), h.buf.size() * sizeof(uint32_t), hipMemcpyHostToDevice) != hipSuccess) {
-      (void)hipGetLastError();
+    launch_crt_tables(cx->tab, P, lm, d, st);
+    if (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess) {
       (void)hipFree(d);
       return nullptr;
     }
-    it = cx->crt.emplace(P, std::make_pair((const uint32_t*)d, h.LM)).first;
+    cx->crt_total += bytes;
+    it = cx->crt.emplace(P, std::make_pair((const uint32_t*)d, lm)).first;
   }
   *LM = it->second.second;
   return it->second.first;

@@ -94,7 +94,8 @@ struct Context {
   double host_us[BIRES_HOST_PHASES] = {0};
   int64_t host_calls = 0;
   std::mutex crt_mu;
-  std::map<int, std::pair<const uint32_t*, int>> crt;  // P -> (device CrtHost buffer, LM)
+  size_t crt_total = 0;                                 // bytes of the CRT tables
+  std::map<int, std::pair<const uint32_t*, int>> crt;  // P -> (device table, LM)
   std::atomic<int> eval_mode{BIRES_EVAL_AUTO};           // evaluation + elimination kernel (BIRES_EVAL_*)
   std::atomic<long long> schur_instances{0}, schur_fallbacks{0};  // Schur kernel statistics
   std::atomic<bool> graphs{false};                       // replay device sequences as captured graphs
@@ -157,8 +158,9 @@ bool interp_tables_device(Context* cx, int blocks, int primes, hipStream_t st, c
 // they would not fit or the build failed: the call then uses the nodes 0..D-1.
 bool geo_tables_device(Context* cx, int D, int P, hipStream_t st, TablesDev* tab);
 
-// Device copy of crt_tables(P), built on first use and kept (nullptr on failure).
-const uint32_t* crt_device(Context* cx, int P, int* LM);
+// The explicit CRT's tables of P primes, built on first use (on stream st, which
+// is then synchronised) and kept; nullptr above 1 GiB in all or on failure.
+const uint32_t* crt_device(Context* cx, int P, hipStream_t st, int* LM);
 // The same when it already exists, else nullptr (never allocates).
 const uint32_t* crt_device_cached(Context* cx, int P, int* LM);
 

@@ -226,17 +226,31 @@ int modular_phase(Context* cx, const Poly& A, const Poly& B, const BigInt& beta,
   return BIRES_OK;
 }
 
-// Mixed-radix reconstruction of `rows` of `src` arrays (row stride ld[j],
-// n[j] coefficients each) over the prime subset S, as symmetric integers.
+// Reconstruction of `src` arrays (row stride ld[j], n[j] coefficients each)
+// over the prime subset S, as symmetric integers: by the explicit CRT when S
+// is the first |S| primes of the table (every prime was lucky) and its
+// operands fit, else in mixed radix with tables made for S.  Where a residue
+// lies within rounding of +-M/2 the two may differ by M; the caller's
+// certificate holds for any representatives within its norm bounds.
 int reconstruct(Context* cx, const std::vector<int>& S, const std::vector<const uint32_t*>& src,
                 const std::vector<int>& ld, const std::vector<int>& n, hipStream_t st, std::vector<Poly>& out) {
   const HostTables& T = host_tables();
-  const int nj = (int)src.size(), P = (int)S.size();
-  std::vector<ModP> primes(P);
-  for (int i = 0; i < P; ++i) primes[i] = T.primes[S[i]];
+  const int nj = (int)src.size(), P = (int)S.size();  // P >= 1
+  int LM = 0;
+  const uint32_t* ct = nullptr;
+  const int cls = crt_class(P);
+  if (S.back() == P - 1 && cls >= 0) ct = crt_device(cx, P, st, &LM);
+  size_t lds = !ct ? 0 : cls == CRT_BIG ? crt_big_lds_bytes(P, LM) : crt_lds_bytes(LM + 1, P);
+  if (ct && (lds > cx->lds_per_block || (cls == CRT_BIG && !crt_big_limbs_ok(LM, LM + 1)))) ct = nullptr;
+  const int Lcap = ct ? LM + 1 : P + 1, Lacc = ct ? 0 : P + 1;
+  const int rows = !ct ? 1 : cls == CRT_BIG ? 32 : crt_rows_per_block(P);
+  std::vector<ModP> primes;
   std::vector<uint32_t> gm, cm, pm, pi;
-  mrc_tables(primes, gm, cm, pm, pi);
-  const int Lcap = P + 1, Lacc = P + 1;
+  if (!ct) {
+    primes.resize(P);
+    for (int i = 0; i < P; ++i) primes[i] = T.primes[S[i]];
+    mrc_tables(primes, gm, cm, pm, pi);
+  }
   Layout L;
   const size_t o_pr = L.take(primes.size() * sizeof(ModP));
   const size_t o_gm = L.take(gm.size() * 4);
@@ -251,7 +265,7 @@ int reconstruct(Context* cx, const std::vector<int>& S, const std::vector<const 
   std::vector<size_t> o_c(nj), o_d(nj), o_n(nj), o_lo(nj), o_hi(nj), o_o(nj);
   for (int j = 0; j < nj; ++j) {
     o_c[j] = L.take((size_t)P * n[j] * 4);
-    o_d[j] = L.take((size_t)P * n[j] * 4);
+    o_d[j] = L.take(ct ? 0 : (size_t)P * n[j] * 4);
     o_n[j] = L.take((size_t)n[j] * 4);
     o_lo[j] = L.take((size_t)n[j] * Lacc * 8);
     o_hi[j] = L.take((size_t)n[j] * Lacc * 4);
@@ -260,11 +274,13 @@ int reconstruct(Context* cx, const std::vector<int>& S, const std::vector<const 
   DevBuf dev(&cx->dev, L.bytes), host(&cx->host, L.bytes);
   if (!dev.p || !host.p) return BIRES_ENOMEM;
   uint8_t* H = host.as<uint8_t>();
-  std::memcpy(H + o_pr, primes.data(), primes.size() * sizeof(ModP));
-  std::memcpy(H + o_gm, gm.data(), gm.size() * 4);
-  std::memcpy(H + o_cm, cm.data(), cm.size() * 4);
-  std::memcpy(H + o_pm, pm.data(), pm.size() * 4);
-  std::memcpy(H + o_pi, pi.data(), pi.size() * 4);
+  if (!ct) {
+    std::memcpy(H + o_pr, primes.data(), primes.size() * sizeof(ModP));
+    std::memcpy(H + o_gm, gm.data(), gm.size() * 4);
+    std::memcpy(H + o_cm, cm.data(), cm.size() * 4);
+    std::memcpy(H + o_pm, pm.data(), pm.size() * 4);
+    std::memcpy(H + o_pi, pi.data(), pi.size() * 4);
+  }
   std::memcpy(H + o_idx, S.data(), (size_t)P * 4);
   JobDev* J = (JobDev*)(H + o_jobs);
   int* st3 = (int*)(H + o_st);
@@ -285,27 +301,35 @@ int reconstruct(Context* cx, const std::vector<int>& S, const std::vector<const 
     J[j].degcap = n[j] - 1;
     J[j].deg_out = dev.as<int32_t>(o_flags) + 2 * j;
     J[j].err = dev.as<int32_t>(o_flags) + 2 * j + 1;
+    J[j].crt = ct;
+    J[j].crt_LM = LM;
     flags[2 * j] = -1;
     flags[2 * j + 1] = 0;
-    st3[j + 1] = st3[j] + n[j];  // mrc
+    st3[j + 1] = st3[j] + (n[j] + rows - 1) / rows;  // crt, mrc
     st3[nj + 1 + j + 1] = st3[nj + 1 + j] + (n[j] * Lacc + 255) / 256;  // limbs_sum
     st3[2 * (nj + 1) + j + 1] = st3[2 * (nj + 1) + j] + (n[j] + 63) / 64;  // limbs_carry
   }
   if (hipMemcpyAsync(dev.p, H, up_end, hipMemcpyHostToDevice, st) != hipSuccess) return BIRES_EDEVICE;
   for (int j = 0; j < nj; ++j)
     launch_gather_rows(src[j], ld[j], dev.as<int>(o_idx), P, n[j], dev.as<uint32_t>(o_c[j]), st);
-  TablesDev tab{};
-  tab.primes = dev.as<ModP>(o_pr);
-  tab.gm = dev.as<uint32_t>(o_gm);
-  tab.cm = dev.as<uint32_t>(o_cm);
-  tab.pm = dev.as<uint32_t>(o_pm);
-  tab.pi = dev.as<uint32_t>(o_pi);
-  tab.K = P;
   const int* dst = dev.as<int>(o_st);
   const JobDev* dj = dev.as<JobDev>(o_jobs);
-  launch_mrc(dj, dst, nj, st3[nj], P, tab, st);
-  launch_limbs_sum(dj, dst + nj + 1, nj, st3[2 * nj + 1], tab, st);
-  launch_limbs_carry(dj, dst + 2 * (nj + 1), nj, st3[3 * nj + 2], Lcap, st);
+  if (ct && cls == CRT_BIG) {
+    launch_crt_big(dj, dst, nj, st3[nj], lds, cx->tab, st);
+  } else if (ct) {
+    launch_crt(dj, dst, nj, st3[nj], P, Lcap, cx->tab, st);
+  } else {
+    TablesDev tab{};
+    tab.primes = dev.as<ModP>(o_pr);
+    tab.gm = dev.as<uint32_t>(o_gm);
+    tab.cm = dev.as<uint32_t>(o_cm);
+    tab.pm = dev.as<uint32_t>(o_pm);
+    tab.pi = dev.as<uint32_t>(o_pi);
+    tab.K = P;
+    launch_mrc(dj, dst, nj, st3[nj], P, tab, st);
+    launch_limbs_sum(dj, dst + nj + 1, nj, st3[2 * nj + 1], tab, st);
+    launch_limbs_carry(dj, dst + 2 * (nj + 1), nj, st3[3 * nj + 2], Lcap, st);
+  }
   if (hipGetLastError() != hipSuccess) return BIRES_EDEVICE;
   for (int j = 0; j < nj; ++j)
     if (hipMemcpyAsync(H + o_o[j], dev.as<uint8_t>(o_o[j]), (size_t)n[j] * Lcap * 4, hipMemcpyDeviceToHost, st) !=

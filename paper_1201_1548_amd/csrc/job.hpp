@@ -34,7 +34,7 @@ struct JobDev {
   int32_t Lacc;             // min(Lcap, P + 1)
   uint32_t* out;            // [(degcap+1)][Lcap] result limbs
   int32_t Lcap, degcap;
-  const uint32_t* crt;      // explicit CRT constants of the job's prime count (CrtHost layout)
+  const uint32_t* crt;      // explicit CRT constants of the job's prime count (layout: launch_crt_tables)
   int32_t crt_LM;           // limbs of M = prod_{k<P} p_k
   int32_t* deg_out;         // highest non-zero coefficient index (init -1)
   int32_t* err;             // set non-zero on a failed internal check

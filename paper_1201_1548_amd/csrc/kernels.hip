@@ -1898,7 +1898,7 @@ __global__ __launch_bounds__(64) void k_limbs_carry(const JobDev* jobs, const in
 // balanced base-256 digits (int8), X = sum_c S_c 256^c where
 // S_c = sum_{k,s} d_ks e_k(c - s).  For one coefficient per row that is a
 // product [rows x 4P] x [4P x byte columns] whose right operand depends only on
-// P (crt_tables builds it in operand order); |S_c| < 2^23 for P <= 128.
+// P (crt.hip builds it in operand order); |S_c| < 2^23 for P <= 128.
 // One wave per 32 NT coefficients of one job, in NT row tiles of 32 (NT = 2
 // up to 48 primes, 1 above, for registers): the lanes form the digit words
 // of their rows' y_k straight into the left operands (lane x + 32 g: row x
@@ -1909,7 +1909,6 @@ __global__ __launch_bounds__(64) void k_limbs_carry(const JobDev* jobs, const in
 // X - t M with a signed carry kept in a register (at NT = 2 every lane has a
 // row of the serial carry chain).  The limbs are staged in LDS rows of sld
 // words and written as one contiguous range.
-constexpr int CRT_MAXP = 128;
 
 // Every lane runs the same instructions: indices past the job's primes or
 // degree bound are clamped for the loads and their values masked to zero, and
@@ -2767,14 +2766,22 @@ void launch_mrc(const JobDev* jobs, const int* starts, int nj, int nblocks, int 
                      tab);
 }
 
-bool crt_ok(int max_primes) { return max_primes <= CRT_MAXP; }
+int crt_class(int primes) {
+  if (primes > CRT_SMALL_PRIMES) return primes <= CRT_MAX_PRIMES ? CRT_BIG : -1;
+  const int ks = (primes + 7) / 8;
+  return ks <= 2 ? 0 : ks <= 4 ? 1 : ks <= 6 ? 2 : ks <= 8 ? 3 : ks <= 12 ? 4 : 5;
+}
+int crt_class_primes(int cls) {
+  const int top[] = {16, 32, 48, 64, 96, CRT_SMALL_PRIMES, CRT_MAX_PRIMES};
+  return top[cls];
+}
 
 int crt_row_stride(int max_lcap) { return max_lcap | 1; }
 
 // Stride of the per-prime constants (even, so that the doubles stay aligned)
 // and the words of M for a prime count (M < 2^(32 P) has at most P words),
 // rounded up to whole column tiles, both sized by the batch's largest prime
-// count rather than CRT_MAXP, which keeps the blocks small.
+// count rather than CRT_SMALL_PRIMES, which keeps the blocks small.
 int crt_const_stride(int max_primes) { return (max_primes + 1) & ~1; }
 static int crt_max_words(int max_primes) { return 8 * ((4 * (max_primes + 1) + 4 + 31) / 32); }
 

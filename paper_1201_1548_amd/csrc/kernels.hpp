@@ -97,10 +97,32 @@ void launch_mrc(const JobDev* jobs, const int* starts, int nj, int nblocks, int 
 // Explicit CRT straight to limbs on the matrix cores (k_crt_mfma): one wave
 // per rows = crt_rows_per_block(max primes) output coefficients,
 // ceil(min(D, degcap + 1) / rows) blocks per job, which also write the job's
-// zero coefficients above them up to degcap; needs crt_ok(max primes), the
-// jobs' crt tables (crt_tables layout) and crt_lds_bytes(max output limbs,
-// max primes) within the LDS per block.
-bool crt_ok(int max_primes);
+// zero coefficients above them up to degcap; needs at most
+// CRT_SMALL_PRIMES, the jobs' crt tables (launch_crt_tables) and
+// crt_lds_bytes(max output limbs, max primes) within the LDS per block.
+// Classes of prime counts: 0..5 one instance of k_crt_mfma each (counts up to
+// crt_class_primes(c)), CRT_BIG k_crt_big; crt_class gives -1 above
+// CRT_MAX_PRIMES.
+constexpr int CRT_SMALL_PRIMES = 128, CRT_MAX_PRIMES = 1024, CRT_BIG = 6, CRT_CLASSES = 7;
+int crt_class(int primes);
+int crt_class_primes(int cls);
+// k_crt_big: blocks of 32 coefficients, LDS crt_big_lds_bytes(P, LM) (the
+// largest of the launch), output rows with crt_big_limbs_ok.
+size_t crt_big_lds_bytes(int P, int LM);
+bool crt_big_limbs_ok(int LM, int lcap);
+void launch_crt_big(const JobDev* jobs, const int* starts, int nj, int nblocks, size_t lds, TablesDev tab,
+                    hipStream_t s);
+// Explicit CRT constants of the first P primes, M = prod_{k<P} p_k: one
+// buffer of crt_table_words(P, LM) words [w (P) | digit rows (P x LM) | M (LM) |
+// pad to 4 words | B] with w[k] the Montgomery form of ((M / p_k) mod p_k)^{-1}
+// mod p_k, LM the limbs of M and row k the balanced base-256 digits of M / p_k
+// (4 per word).  B is the int8 operand of the matrix-core CRT: entry
+// (k, s; c) = digit c - s of M / p_k (zero outside 0..4 LM - 1) for
+// contraction index 4 k + s and byte column c, in operand order: for column
+// tile ct (32 columns) and contraction step ks (32 indices, 8 primes) one 1 KiB
+// block whose lane x + 32 g holds column 32 ct + x, indices 32 ks + 16 g + 0..15.
+size_t crt_table_words(int P, int LM);
+void launch_crt_tables(TablesDev tab, int P, int LM, uint32_t* buf, hipStream_t s);
 size_t crt_lds_bytes(int max_lcap, int max_primes);
 size_t crt_lds_bytes_rows(int max_lcap, int max_primes, int rows);
 // the CRT's LDS strides: limb rows (sld) and prime constants (cps)
