@@ -325,8 +325,8 @@ int bires_debug_values(const bires_bipoly *f, const bires_bipoly *g, int kind, i
 int bires_set_schedule(int schedule);
 
 /* Evaluation + elimination kernel of the staged schedule.
- *   BIRES_EVAL_AUTO (default): jobs with 1 <= min(m, n) and max(m, n) < 32
- *     (m, n: degrees in the eliminated variable) keep f's coefficient array in
+ *   BIRES_EVAL_AUTO (default): jobs with 1 <= min(m, n) and max(m, n) < 68
+ *     (m, n: degrees in the eliminated variable) keep the coefficient arrays in
  *     registers; blocks that meet a vanishing leading coefficient or a
  *     degree drop are recomputed by the general kernel; other jobs use it;
  *   BIRES_EVAL_LDS: every job uses the general kernel (both arrays in LDS);

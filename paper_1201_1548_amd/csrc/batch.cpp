@@ -55,7 +55,7 @@ struct Work {
   Plan pl;
   int status = BIRES_OK;
   bool active = false;  // goes through the kernels
-  int Lout = 1, degcap = 0, Tf = 0, Tg = 0, ldg = 0, Lacc = 1;
+  int Lout = 1, degcap = 0, Tf = 0, Tg = 0, ldg = 0, Lacc = 1, dig = 0;
   const uint32_t* dev_f = nullptr;
   const uint32_t* dev_g = nullptr;
   size_t o_in[2] = {0, 0}, o_scan[2] = {0, 0};
@@ -464,18 +464,18 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
   // per-kernel first block of each job (prefix sums of the per-job block counts)
   // eval_elim runs one launch per size bucket (LDS per block sized for the
   // bucket, so small jobs are not held to the occupancy of the largest)
-  // jobs whose f array fits in registers (eval_elim_rg_capacity 24, 32 or 64)
-  // run in three more launches
+  // jobs whose arrays fit in registers (eval_elim_rg_capacity) run in one more
+  // launch per capacity
   // jobs on the Schur kernel (wave per instance; 1 or 2 generator rows per
   // lane) in two more
   enum {
-    K_RED, K_IP, K_MRC, K_SUM, K_CAR, K_CRT0, K_EE0 = K_CRT0 + CRT_CLASSES, NBUCKET = 5, K_RG0 = K_EE0 + NBUCKET, NRG = 3,
+    K_RED, K_IP, K_MRC, K_SUM, K_CAR, K_CRT0, K_EE0 = K_CRT0 + CRT_CLASSES, NBUCKET = 5, K_RG0 = K_EE0 + NBUCKET, NRG = 4,
     K_SC0 = K_RG0 + NRG, NSC = 2, K_GE0 = K_SC0 + NSC, NK = K_GE0 + GEO_CLASSES
   };
   const int bucket_words[NBUCKET] = {24, 40, 64, 96, 1 << 30};
-  const int rg_cap[NRG] = {24, 32, 64};
+  const int rg_cap[NRG] = {24, 32, 48, 68};
   int bw[NBUCKET] = {0}, br_[NBUCKET] = {0};
-  int rdeg[NRG] = {0}, rw[NRG] = {0};
+  int rw[NRG] = {0};
   int sw[NSC] = {0};
   int gmax[GEO_CLASSES] = {0};  // interpolation on the geometric nodes: largest D of each class
   std::vector<int> starts[NK];
@@ -503,7 +503,7 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
     const Plan& p = x.pl;
     x.o_res_f = ws.take((size_t)p.P * x.Tf * 4);
     x.o_res_g = ws.take((size_t)p.P * x.Tg * 4);
-    (void)ws.take(128);  // whole-chunk loads of the evaluation may read past the last row
+    (void)ws.take(EE_SLACK_BYTES);  // whole-chunk loads of the evaluation may read past the last row
     x.o_vals = ws.take((size_t)p.P * p.D * 4);
     if (!debug) {
       x.o_coefs = ws.take((size_t)p.P * p.D * 4);
@@ -525,9 +525,10 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
       starts[K_SC0 + nr - 1][i + 1] = p.P * p.D;
       sw[nr - 1] = std::max(sw[nr - 1], p.m + p.n + 2);
     } else if (rc) {
-      const int r = rc == rg_cap[0] ? 0 : rc == rg_cap[1] ? 1 : 2;
+      int r = 0;
+      while (rg_cap[r] != rc) ++r;
+      x.dig = sched != BIRES_SCHEDULE_FUSED;  // (the persistent launch reads plain residues)
       starts[K_RG0 + r][i + 1] = p.P * ((p.D + 63) / 64);
-      rdeg[r] = std::max(rdeg[r], std::max(p.m, p.n));
       rw[r] = std::max(rw[r], p.m + p.n + 2);
     } else {
       int bk = 0;
@@ -759,6 +760,7 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
     std::memcpy(rd, rowdeg.data() + rd_off[i], sizeof(int32_t) * (size_t)(p.m + p.n + 2));
     J.rowdeg_f = (const int32_t*)(D0 + x.o_rowdeg);
     J.rowdeg_g = J.rowdeg_f + p.m + 1;
+    J.dig = x.dig;
     J.res_f = (uint32_t*)(D0 + x.o_res_f);
     J.res_g = (uint32_t*)(D0 + x.o_res_g);
     J.vals = (uint32_t*)(D0 + x.o_vals);
@@ -969,9 +971,9 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
           launch_eval_elim(d_jobs, st_of(K_EE0 + bk), nj, nb_of(K_EE0 + bk), bw[bk], br_[bk], etab, st);
       }
       for (int r = 0; r < NRG; ++r) {
-        sg.add(nb_of(K_RG0 + r), rdeg[r], rw[r], o_fbc, o_fbq[r]);
+        sg.add(nb_of(K_RG0 + r), rw[r], o_fbc, o_fbq[r]);
         if (run && nb_of(K_RG0 + r))
-          launch_eval_elim_rg(rg_cap[r], d_jobs, st_of(K_RG0 + r), nj, nb_of(K_RG0 + r), rdeg[r], rw[r],
+          launch_eval_elim_rg(rg_cap[r], d_jobs, st_of(K_RG0 + r), nj, nb_of(K_RG0 + r), rw[r],
                               (int*)(D0 + o_fbc) + r, (int*)(D0 + o_fbq[r]), etab, st);
       }
       for (int r = 0; r < NSC; ++r) {

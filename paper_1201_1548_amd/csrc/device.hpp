@@ -130,4 +130,36 @@ __device__ __forceinline__ uint32_t eval_point(const TablesDev& tab, int k, int 
 typedef int im_v4i __attribute__((ext_vector_type(4)));
 typedef int im_v16i __attribute__((ext_vector_type(16)));
 
+// Byte offset of element (row, idx) of a digit plane of the matrix-core
+// interpolation with Kp = padded contraction length, in operand order: 1 KiB
+// blocks per (32-row tile, 32-wide step), lane l of an operand holding row
+// l % 32 and contraction indices 16 (l / 32) + 0..15.
+__device__ __forceinline__ size_t im_off(int row, int idx, int Kp) {
+  const int rt = row >> 5, r = row & 31, ks = idx >> 5, g = (idx >> 4) & 1, b = idx & 15;
+  return ((((size_t)rt * (Kp >> 5) + ks) * 64) + r + 32 * g) * 16 + b;
+}
+
+// The value v = R(a) mod p_k (plain residue) of point a of job J: into vals,
+// or for a job of the matrix-core interpolation group straight into the
+// group's four digit planes of prime k (column ycol), which the
+// interpolation reads as its right operand.  Those planes are not cleared:
+// columns past the group only reach output columns that are not written,
+// and points in [D, Dp) meet zero entries of the inverse Vandermonde planes.
+// (A call, not inlined: the register allocation of the evaluation kernels'
+// loops stays that of a single store.)
+static __device__ __noinline__ void put_planes(int8_t* yp, int ycol, int ynp, int ydp, int k, int a, uint32_t v, uint32_t p) {
+  const size_t plane = (size_t)ynp * ydp;
+  int8_t* base = yp + (size_t)k * 4 * plane + im_off(ycol, a, ydp);
+  const uint32_t d = digits4(v, p);
+#pragma unroll
+  for (int s = 0; s < 4; ++s) base[s * plane] = (int8_t)(d >> (8 * s));
+}
+
+__device__ __forceinline__ void put_value(const JobDev& J, int k, int a, uint32_t v, uint32_t p) {
+  if (J.yp)
+    put_planes(J.yp, J.ycol, J.ynp, J.ydp, k, a, v, p);
+  else
+    J.vals[(size_t)k * J.D + a] = v;
+}
+
 }  // namespace bires

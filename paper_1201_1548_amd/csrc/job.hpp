@@ -25,6 +25,7 @@ struct JobDev {
   const int32_t* rowdeg_g;  // [n+1]
   uint32_t* res_f;          // [P][Tf] Montgomery residues
   uint32_t* res_g;          // [P][Tg]
+  int32_t dig;              // 1: the residues are stored as balanced base-256 digit words (digits4)
   uint32_t* vals;           // [P][D] values R(a) mod p_k, a = 0..D-1
   uint32_t* coefs;          // [P][D] coefficients of R mod p_k
   uint32_t* digits;         // [P][D] mixed-radix digits

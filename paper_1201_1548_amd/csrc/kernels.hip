@@ -6,8 +6,8 @@
 //   k_transpose   exchange x and y in a limb rectangle (res_x, disc_x)
 //   k_reduce      (a) coefficients modulo each prime, Montgomery form
 //   k_eval_elim   (b)+(c) evaluate at x = a and take the univariate resultant
-//                 over F_p, one lane per (prime, point); k_eval_elim_rg24,
-//                 _rg32 and _rg64 keep f's coefficient array in registers
+//                 over F_p, one lane per (prime, point), both coefficient
+//                 arrays in LDS (the register kernels are in ee.hip)
 //   k_schur       (c) the same elimination by the Schur algorithm on the
 //                 displacement generators, one wave per (prime, point)
 //   k_psc         principal subresultant coefficients mod p, one lane per point
@@ -192,7 +192,7 @@ __device__ void dev_reduce(const JobDev& J, int lb, int k0, int k1, TablesDev ta
         uint32_t x = mmul(w0, q.r2, q);
         if (neg) x = msub(x, q.r2, q.p);
         if (mult) x = mmul(x, to_mont(mult, q), q);
-        dst[(size_t)(kb + j) * T] = x;
+        dst[(size_t)(kb + j) * T] = J.dig ? digits4(x, q.p) : x;
       }
     }
     return;
@@ -204,7 +204,7 @@ __device__ void dev_reduce(const JobDev& J, int lb, int k0, int k1, TablesDev ta
     for (int l = L - 1; l >= 0; --l) x = mdot2(x, q.r2, reduce32(src[l], q.p), q.r2, q);
     if (negv) x = msub(x, mpow(q.r2, (uint32_t)L, q), q.p);
     if (mult) x = mmul(x, to_mont(mult, q), q);
-    dst[(size_t)k * T] = x;
+    dst[(size_t)k * T] = J.dig ? digits4(x, q.p) : x;
   }
 }
 
@@ -393,38 +393,6 @@ __device__ uint32_t uni_resultant(uint32_t* A, uint32_t* B, int m, int n, const 
 // of EV_PW, combined by Horner's rule in a^EV_PW.
 constexpr int EV_PW = 24;
 
-// Byte offset of element (row, idx) of a digit plane of the matrix-core
-// interpolation with Kp = padded contraction length, in operand order: 1 KiB
-// blocks per (32-row tile, 32-wide step), lane l of an operand holding row
-// l % 32 and contraction indices 16 (l / 32) + 0..15.
-__device__ __forceinline__ size_t im_off(int row, int idx, int Kp) {
-  const int rt = row >> 5, r = row & 31, ks = idx >> 5, g = (idx >> 4) & 1, b = idx & 15;
-  return ((((size_t)rt * (Kp >> 5) + ks) * 64) + r + 32 * g) * 16 + b;
-}
-
-// The value v = R(a) mod p_k (plain residue) of point a of job J: into vals,
-// or for a job of the matrix-core interpolation group straight into the
-// group's four digit planes of prime k (column ycol), which the
-// interpolation reads as its right operand.  Those planes are not cleared:
-// columns past the group only reach output columns that are not written,
-// and points in [D, Dp) meet zero entries of the inverse Vandermonde planes.
-// (A call, not inlined: the register allocation of the evaluation kernels'
-// loops stays that of a single store.)
-__device__ __noinline__ void put_planes(int8_t* yp, int ycol, int ynp, int ydp, int k, int a, uint32_t v, uint32_t p) {
-  const size_t plane = (size_t)ynp * ydp;
-  int8_t* base = yp + (size_t)k * 4 * plane + im_off(ycol, a, ydp);
-  const uint32_t d = digits4(v, p);
-#pragma unroll
-  for (int s = 0; s < 4; ++s) base[s * plane] = (int8_t)(d >> (8 * s));
-}
-
-__device__ __forceinline__ void put_value(const JobDev& J, int k, int a, uint32_t v, uint32_t p) {
-  if (J.yp)
-    put_planes(J.yp, J.ycol, J.ynp, J.ydp, k, a, v, p);
-  else
-    J.vals[(size_t)k * J.D + a] = v;
-}
-
 // Read-only data with wave-uniform addresses, read through the scalar cache.
 typedef __attribute__((address_space(4))) const uint32_t cu32;
 typedef __attribute__((address_space(4))) const u32x4 cu4;
@@ -439,7 +407,13 @@ typedef __attribute__((address_space(4))) const int32_t ci32;
 // past the end of a short row: the residue buffers are followed by at least
 // that much workspace.  Eight products of residues stay below 8 p^2 < 2^64
 // (p < 2^32 / 3), so each 64-bit partial sum takes eight.
-template <class C, class C4, int NPW>
+// DIG: the residues are stored as balanced digit words (JobDev::dig).
+__device__ __forceinline__ uint32_t undigits(uint32_t w, uint32_t p) {
+  const uint32_t v = (w ^ 0x808080u) - 0x808080u;  // the symmetric representative
+  return umin32(v, v + p);
+}
+
+template <class C, class C4, int NPW, bool DIG = false>
 __device__ __forceinline__ uint32_t eval_row(C* c, int d, const uint32_t (&pw)[NPW], uint32_t apw, const ModP& q) {
   static_assert(NPW % 8 == 0, "powers come in groups of eight");
   if (d < 0) return 0u;
@@ -450,7 +424,11 @@ __device__ __forceinline__ uint32_t eval_row(C* c, int d, const uint32_t (&pw)[N
     const int ng = (min(NPW, d + 1 - ch * NPW) + 3) >> 2;
     u32x4 v[NPW / 4];
 #pragma unroll
-    for (int g = 0; g < NPW / 4; ++g) v[g] = cc[g];
+    for (int g = 0; g < NPW / 4; ++g) {
+      v[g] = cc[g];
+      if constexpr (DIG)
+        v[g] = (u32x4){undigits(v[g].x, q.p), undigits(v[g].y, q.p), undigits(v[g].z, q.p), undigits(v[g].w, q.p)};
+    }
     // The products are v_mad_u64_u32 with the 32-bit power as an operand.
     // Written in C, (uint64_t) pw[i] * c lets the compiler hoist the
     // zero-extended powers out of the row loop as 64-bit register pairs,
@@ -490,7 +468,7 @@ __device__ __forceinline__ uint32_t eval_row(C* c, int d, const uint32_t (&pw)[N
 // them itself, uses ordinary loads.
 // f(a, y) and g(a, y) modulo p_k (Montgomery form) at the point a (Montgomery
 // form aM) into the lane arrays A[j W], B[j W] (ascending powers of y).
-template <int W, bool SC>
+template <int W, bool SC, bool DIG = false>
 __device__ __forceinline__ void eval_pair(const JobDev& J, int k, uint32_t aM, const ModP& q, uint32_t* A,
                                           uint32_t* B) {
   typedef typename std::conditional<SC, cu32, const uint32_t>::type RW;
@@ -509,12 +487,12 @@ __device__ __forceinline__ void eval_pair(const JobDev& J, int k, uint32_t aM, c
   for (int i = 1; i < EV_PW; ++i) pw[i] = i <= dmax ? mmul(pw[i - 1], aM, q) : 0u;
   const uint32_t apw = dmax >= EV_PW ? mmul(pw[EV_PW - 1], aM, q) : 0u;
   for (int j = 0; j <= m; ++j)
-    A[j * W] = eval_row<RW, RW4>(Rf + j * lpf, __builtin_amdgcn_readfirstlane(RDf[j]), pw, apw, q);
+    A[j * W] = eval_row<RW, RW4, EV_PW, DIG>(Rf + j * lpf, __builtin_amdgcn_readfirstlane(RDf[j]), pw, apw, q);
   for (int j = 0; j <= n; ++j)
-    B[j * W] = eval_row<RW, RW4>(Rg + j * lpg, __builtin_amdgcn_readfirstlane(RDg[j]), pw, apw, q);
+    B[j * W] = eval_row<RW, RW4, EV_PW, DIG>(Rg + j * lpg, __builtin_amdgcn_readfirstlane(RDg[j]), pw, apw, q);
 }
 
-template <int W, bool SC>
+template <int W, bool SC, bool DIG = false>
 __device__ __forceinline__ void dev_eval_elim(const JobDev& J, int lb, TablesDev tab, uint32_t* lds) {
   const int nbpp = (J.D + W - 1) / W;
   const int k = lb / nbpp;
@@ -525,7 +503,7 @@ __device__ __forceinline__ void dev_eval_elim(const JobDev& J, int lb, TablesDev
   const int pt = a0 + lane_id();
   if (pt >= J.D) return;
   const ModP q = tab.primes[k];
-  eval_pair<W, SC>(J, k, eval_point(tab, k, pt, q), q, A, B);
+  eval_pair<W, SC, DIG>(J, k, eval_point(tab, k, pt, q), q, A, B);
   const uint32_t r = uni_resultant<W>(A, B, m, n, q);
   put_value(J, k, pt, from_mont(r, q), q.p);
 }
@@ -771,22 +749,6 @@ __device__ __forceinline__ bool dev_eval_elim_rg(const JobDev& J, int lb, Tables
     as = bs;
     bs -= 1;
   }
-  if constexpr (C > 32) {
-    // steps above the unrolled chain's reach (B > 30): the fused step with
-    // wave-uniform guards (a normal step: d = 0 and a b even, so only pfx
-    // and den change)
-    while (bs > 30) {
-      bool short_rem;
-      const uint32_t lb = areg ? rg_step<C, true>(X, L, as, bs, &short_rem, q)
-                               : rg_step<C, false>(X, L, as, bs, &short_rem, q);
-      if (short_rem) return false;
-      pfx = mmul(pfx, mmul(lb, lb, q), q);
-      den = mmul(den, pfx, q);
-      areg = !areg;
-      as = bs;
-      bs -= 1;
-    }
-  }
   uint32_t last;
   if (bs == 0) {
     // the constant remainder is in the array that does not hold A
@@ -805,49 +767,7 @@ __device__ __forceinline__ bool dev_eval_elim_rg(const JobDev& J, int lb, Tables
   return true;
 }
 
-template <int C>
-__device__ __forceinline__ void eval_elim_rg_block(const JobDev* jobs, const int* starts, int nj, TablesDev tab,
-                                                   int* fb_count, int* fb_queue, uint32_t* lds) {
-  const int b = xcd_block(blockIdx.x, gridDim.x);
-  const int job = find_job(starts, nj, b, gridDim.x);
-  const bool ok = dev_eval_elim_rg<C>(jobs[job], b - starts[job], tab, lds);
-  if (__ballot(!ok) != 0ull && threadIdx.x == 0) fb_queue[atomicAdd(fb_count, 1)] = b;
-}
-
-// C = 24 is held to RG24_WAVES waves per SIMD (76 VGPRs, no spills); C = 32
-// runs at RG32_WAVES (102 VGPRs; at 5 waves it spills inside the chain).
-#ifndef RG24_WAVES
-#define RG24_WAVES 6
-#endif
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(RG24_WAVES, 8))) void k_eval_elim_rg24(
-    const JobDev* jobs, const int* starts, int nj, TablesDev tab, int* fb_count, int* fb_queue) {
-  extern __shared__ __align__(16) uint32_t lds[];
-  eval_elim_rg_block<24>(jobs, starts, nj, tab, fb_count, fb_queue, lds);
-}
-
-#ifndef RG32_WAVES
-#define RG32_WAVES 4
-#endif
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(RG32_WAVES, 8))) void k_eval_elim_rg32(
-    const JobDev* jobs, const int* starts, int nj, TablesDev tab, int* fb_count, int* fb_queue) {
-  extern __shared__ __align__(16) uint32_t lds[];
-  eval_elim_rg_block<32>(jobs, starts, nj, tab, fb_count, fb_queue, lds);
-}
-
-// C = 64 (jobs with 32 <= max(m, n) < 64): the steps above degree 30 run the
-// guarded fused step in a loop, the rest the unrolled chain.  Its LDS (65
-// words per lane) allows 9 blocks per CU, against 4 for the LDS kernel at
-// m = n = 63.
-#ifndef RG64_WAVES
-#define RG64_WAVES 2
-#endif
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(RG64_WAVES, 8))) void k_eval_elim_rg64(
-    const JobDev* jobs, const int* starts, int nj, TablesDev tab, int* fb_count, int* fb_queue) {
-  extern __shared__ __align__(16) uint32_t lds[];
-  eval_elim_rg_block<64>(jobs, starts, nj, tab, fb_count, fb_queue, lds);
-}
-
-// The queued blocks of k_eval_elim_rg, recomputed with the general kernel.
+// The queued blocks of k_eval_elim_ee*, recomputed with the general kernel.
 __global__ __launch_bounds__(64) void k_eval_elim_fb(const JobDev* jobs, const int* starts, int nj, TablesDev tab,
                                                      const int* fb_count, const int* fb_queue) {
   extern __shared__ __align__(16) uint32_t lds[];
@@ -855,7 +775,7 @@ __global__ __launch_bounds__(64) void k_eval_elim_fb(const JobDev* jobs, const i
   for (int i = blockIdx.x; i < cnt; i += gridDim.x) {
     const int b = fb_queue[i];
     const int job = find_job(starts, nj, b);
-    dev_eval_elim<64, true>(jobs[job], b - starts[job], tab, lds);
+    dev_eval_elim<64, true, true>(jobs[job], b - starts[job], tab, lds);
   }
 }
 
@@ -2692,21 +2612,8 @@ void launch_eval_elim(const JobDev* jobs, const int* starts, int nj, int nblocks
                      starts, nj, tab);
 }
 
-int eval_elim_rg_capacity(int m, int n) {
-  if (m < 1 || n < 1) return 0;
-  const int d = std::max(m, n);
-  return d < 24 ? 24 : d < 32 ? 32 : d < 64 ? 64 : 0;
-}
-
-void launch_eval_elim_rg(int C, const JobDev* jobs, const int* starts, int nj, int nblocks, int max_deg,
-                         int max_words, int* fb_count, int* fb_queue, TablesDev tab, hipStream_t s) {
-  const size_t lds = (size_t)(max_deg + 1) * 64 * sizeof(uint32_t);
-  if (C == 24)
-    hipLaunchKernelGGL(k_eval_elim_rg24, dim3(nblocks), dim3(64), lds, s, jobs, starts, nj, tab, fb_count, fb_queue);
-  else if (C == 32)
-    hipLaunchKernelGGL(k_eval_elim_rg32, dim3(nblocks), dim3(64), lds, s, jobs, starts, nj, tab, fb_count, fb_queue);
-  else
-    hipLaunchKernelGGL(k_eval_elim_rg64, dim3(nblocks), dim3(64), lds, s, jobs, starts, nj, tab, fb_count, fb_queue);
+void launch_eval_elim_fb(const JobDev* jobs, const int* starts, int nj, int nblocks, int max_words,
+                         const int* fb_count, const int* fb_queue, TablesDev tab, hipStream_t s) {
   hipLaunchKernelGGL(k_eval_elim_fb, dim3(std::min(nblocks, 256)), dim3(64), eval_elim_lds_bytes(max_words, 0), s,
                      jobs, starts, nj, tab, fb_count, fb_queue);
 }

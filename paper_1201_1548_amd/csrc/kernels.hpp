@@ -40,17 +40,21 @@ inline int pad4(int ld) { return (ld + 3) & ~3; }
 size_t eval_elim_lds_bytes(int words, int res);
 void launch_eval_elim(const JobDev* jobs, const int* starts, int nj, int nblocks, int max_words, int max_res,
                       TablesDev tab, hipStream_t s);
-// Evaluation + elimination with f's coefficient array in registers: the
-// register capacity C (24, 32 or 64) for a job of degrees m, n in the
+// Evaluation + elimination with both coefficient arrays in registers (ee.hip):
+// the register capacity C (24, 32, 48 or 68) for a job of degrees m, n in the
 // eliminated variable, or 0 when the job needs the LDS kernel (min(m, n) = 0
-// or max(m, n) >= 64).  launch_eval_elim_rg runs the blocks of jobs with that
-// capacity (max_deg = max over jobs of max(m, n), max_words of m + n + 2),
-// then recomputes with launch_eval_elim's kernel the blocks that leave the
-// uniform normal case.  fb_count: one device int, zero before the launch;
-// fb_queue: nblocks ints of workspace.
+// or max(m, n) >= 68).  launch_eval_elim_rg runs the blocks of jobs with that
+// capacity, whose residues are digit words (JobDev::dig) followed by at least
+// EE_SLACK_BYTES of workspace, then recomputes with the LDS kernel (max_words:
+// max over jobs of m + n + 2) the blocks that leave the uniform normal case.
+// fb_count: one device int, zero before the launch; fb_queue: nblocks ints of
+// workspace.
+constexpr size_t EE_SLACK_BYTES = 512;
 int eval_elim_rg_capacity(int m, int n);
-void launch_eval_elim_rg(int C, const JobDev* jobs, const int* starts, int nj, int nblocks, int max_deg,
-                         int max_words, int* fb_count, int* fb_queue, TablesDev tab, hipStream_t s);
+void launch_eval_elim_rg(int C, const JobDev* jobs, const int* starts, int nj, int nblocks, int max_words,
+                         int* fb_count, int* fb_queue, TablesDev tab, hipStream_t s);
+void launch_eval_elim_fb(const JobDev* jobs, const int* starts, int nj, int nblocks, int max_words,
+                         const int* fb_count, const int* fb_queue, TablesDev tab, hipStream_t s);
 // Evaluation + elimination by the Schur algorithm on the displacement
 // generators, one wave (block of 64) per (prime, point) instance: P * D blocks
 // per job; rows per lane NR = schur_rows_per_lane(m, n) (0: the job cannot
