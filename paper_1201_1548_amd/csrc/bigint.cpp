@@ -1,5 +1,6 @@
-// Host big-integer helpers (see bigint.hpp).  Division is Knuth's algorithm D
-// (TAOCP vol. 2, 4.3.1) on 32-bit digits with 64-bit intermediates.
+// Host big-integer helpers (see bigint.hpp).  General division is Knuth's
+// algorithm D (TAOCP vol. 2, 4.3.1) on 32-bit digits with 64-bit intermediates;
+// exact division and the gcd run on 64-bit limbs.
 #include "bigint.hpp"
 
 #include <algorithm>
@@ -108,6 +109,21 @@ BigInt big_add(const BigInt& a, const BigInt& b) {
   return r;
 }
 
+void big_sub_from(BigInt& a, const BigInt& b) {
+  if (b.is_zero()) return;
+  if (a.is_zero() || a.neg == b.neg) {
+    if (cmp_mag(a.mag, b.mag) >= 0) {
+      a.mag = sub_mag(a.mag, b.mag);
+      if (a.mag.empty()) a.neg = false;
+    } else {
+      a.mag = sub_mag(b.mag, a.mag);
+      a.neg = !b.neg;
+    }
+  } else {
+    a.mag = add_mag(a.mag, b.mag);
+  }
+}
+
 BigInt big_mul(const BigInt& a, const BigInt& b) {
   BigInt r;
   if (a.is_zero() || b.is_zero()) return r;
@@ -201,29 +217,178 @@ void divmod_mag(const std::vector<uint32_t>& a, const std::vector<uint32_t>& b, 
   trim(r);
 }
 
-bool big_divexact(const BigInt& a, const BigInt& b, BigInt& q) {
-  std::vector<uint32_t> r;
-  divmod_mag(a.mag, b.mag, q.mag, r);
-  if (!r.empty()) return false;
-  q.neg = (a.neg != b.neg) && !q.mag.empty();
+namespace {
+
+typedef unsigned __int128 u128;
+typedef __int128 s128;
+
+// Magnitudes in 64-bit limbs, for the quadratic loops.
+void to64(const std::vector<uint32_t>& m, std::vector<uint64_t>& w) {
+  const size_t n = (m.size() + 1) / 2;
+  w.resize(n);
+  for (size_t i = 0; i < n; ++i)
+    w[i] = m[2 * i] | (2 * i + 1 < m.size() ? (uint64_t)m[2 * i + 1] << 32 : 0);
+}
+
+void from64(const uint64_t* w, size_t n, std::vector<uint32_t>& m) {
+  m.resize(2 * n);
+  for (size_t i = 0; i < n; ++i) {
+    m[2 * i] = (uint32_t)w[i];
+    m[2 * i + 1] = (uint32_t)(w[i] >> 32);
+  }
+  trim(m);
+}
+
+void trim64(std::vector<uint64_t>& w) {
+  while (!w.empty() && w.back() == 0) w.pop_back();
+}
+
+// w >> s, s < 64.
+void shift_down(std::vector<uint64_t>& w, int s) {
+  if (s)
+    for (size_t i = 0; i < w.size(); ++i) w[i] = (w[i] >> s) | (i + 1 < w.size() ? w[i + 1] << (64 - s) : 0);
+  trim64(w);
+}
+
+// The bits [at, at + 62) of w.
+uint64_t window(const std::vector<uint64_t>& w, size_t at) {
+  const size_t i = at / 64, s = at % 64;
+  uint64_t v = i < w.size() ? w[i] >> s : 0;
+  if (s && i + 1 < w.size()) v |= w[i + 1] << (64 - s);
+  return v & (((uint64_t)1 << 62) - 1);
+}
+
+}  // namespace
+
+ExactDiv::ExactDiv(const BigInt& b) : neg_(b.neg), one_(b.mag.size() == 1 && b.mag[0] == 1u) {
+  to64(b.mag, d_);
+  while (d_[zeros_] == 0) ++zeros_;
+  d_.erase(d_.begin(), d_.begin() + zeros_);
+  shift_ = __builtin_ctzll(d_[0]);
+  shift_down(d_, shift_);
+  inv_ = d_[0];  // Newton: right in 3 bits, doubled five times
+  for (int i = 0; i < 5; ++i) inv_ *= 2 - d_[0] * inv_;
+}
+
+bool ExactDiv::operator()(const BigInt& a, BigInt& q) {
+  const bool neg = a.neg != neg_;
+  if (one_ || a.is_zero()) {
+    q.mag = a.mag;
+    q.neg = neg && !q.mag.empty();
+    return true;
+  }
+  to64(a.mag, t_);
+  if (t_.size() <= zeros_) return false;
+  for (size_t i = 0; i < zeros_; ++i)
+    if (t_[i]) return false;
+  t_.erase(t_.begin(), t_.begin() + zeros_);
+  if (t_[0] & (((uint64_t)1 << shift_) - 1)) return false;
+  shift_down(t_, shift_);
+  const size_t n = t_.size(), m = d_.size();
+  if (n < m) return false;
+  // quotient limbs from the low end: limb i cancels limb i of what is left
+  for (size_t i = 0; i + m <= n; ++i) {
+    const uint64_t x = t_[i] * inv_;
+    uint64_t carry = 0;
+    for (size_t j = 0; j < m; ++j) {
+      const u128 p = (u128)x * d_[j] + carry;
+      const uint64_t lo = (uint64_t)p;
+      carry = (uint64_t)(p >> 64) + (t_[i + j] < lo);
+      t_[i + j] -= lo;
+    }
+    for (size_t k = i + m; carry && k < n; ++k) {
+      const uint64_t v = t_[k];
+      t_[k] = v - carry;
+      carry = v < carry;
+    }
+    if (carry) return false;
+    t_[i] = x;
+  }
+  for (size_t k = n - m + 1; k < n; ++k)
+    if (t_[k]) return false;
+  from64(t_.data(), n - m + 1, q.mag);
+  q.neg = neg && !q.mag.empty();
   return true;
 }
 
+bool big_divexact(const BigInt& a, const BigInt& b, BigInt& q) {
+  ExactDiv d(b);
+  return d(a, q);
+}
+
+// Lehmer's algorithm (TAOCP vol. 2, 4.5.2, Algorithm L): the quotients of the
+// leading 62 bits, as long as both ends of their interval agree and the
+// cofactors stay below 2^31, are applied to the numbers at once.
 BigInt big_gcd(const BigInt& a, const BigInt& b) {
-  std::vector<uint32_t> x = a.mag, y = b.mag, q, r;
-  while (!y.empty()) {
-    divmod_mag(x, y, q, r);
-    x.swap(y);
-    y.swap(r);
+  std::vector<uint64_t> x, y, z;
+  to64(a.mag, x);
+  to64(b.mag, y);
+  std::vector<uint32_t> x32, y32, q32, r32;
+  if (cmp_mag(a.mag, b.mag) < 0) x.swap(y);
+  while (y.size() > 1) {
+    // x >= y; the window holds the leading 62 bits of x
+    const size_t bits = 64 * x.size() - (size_t)__builtin_clzll(x.back());
+    uint64_t u = window(x, bits - 62), v = window(y, bits - 62);
+    int64_t A = 1, B = 0, C = 0, D = 1;
+    while ((int64_t)v + C > 0 && (int64_t)v + D > 0) {
+      const uint64_t q = (uint64_t)((int64_t)u + A) / (uint64_t)((int64_t)v + C);
+      if (q != (uint64_t)((int64_t)u + B) / (uint64_t)((int64_t)v + D)) break;
+      const s128 c = (s128)A - (s128)q * C, d = (s128)B - (s128)q * D;
+      const s128 lim = (s128)1 << 31;
+      if (c >= lim || c <= -lim || d >= lim || d <= -lim) break;
+      A = C, B = D, C = (int64_t)c, D = (int64_t)d;
+      const uint64_t t = u - q * v;
+      u = v;
+      v = t;
+    }
+    if (B == 0) {  // the first quotient is not certain or too long: one division
+      from64(x.data(), x.size(), x32);
+      from64(y.data(), y.size(), y32);
+      divmod_mag(x32, y32, q32, r32);
+      x.swap(y);
+      to64(r32, y);
+      continue;
+    }
+    z.assign(x.size(), 0);
+    s128 cx = 0, cy = 0;
+    for (size_t i = 0; i < x.size(); ++i) {
+      const uint64_t xi = x[i], yi = i < y.size() ? y[i] : 0;
+      cx += (s128)A * xi + (s128)B * yi;
+      cy += (s128)C * xi + (s128)D * yi;
+      x[i] = (uint64_t)cx;
+      z[i] = (uint64_t)cy;
+      cx >>= 64;
+      cy >>= 64;
+    }
+    trim64(x);
+    trim64(z);
+    y.swap(z);
   }
   BigInt g;
-  g.mag = x;
-  return g;
+  if (y.empty()) {
+    from64(x.data(), x.size(), g.mag);
+    return g;
+  }
+  uint64_t s = y[0], r = 0;
+  for (size_t i = x.size(); i-- > 0;) r = (uint64_t)(((u128)r << 64 | x[i]) % s);
+  while (r) {
+    const uint64_t t = s % r;
+    s = r;
+    r = t;
+  }
+  return BigInt::from_u64(s);
 }
 
 uint32_t big_mod_small(const BigInt& a, uint32_t p) {
+  // Barrett: the quotient by the reciprocal is short by at most two
+  const uint64_t inv = ~(uint64_t)0 / p;
   uint64_t rem = 0;
-  for (size_t i = a.mag.size(); i-- > 0;) rem = ((rem << 32) | a.mag[i]) % p;
+  for (size_t i = a.mag.size(); i-- > 0;) {
+    const uint64_t t = (rem << 32) | a.mag[i];
+    rem = t - (uint64_t)((u128)t * inv >> 64) * p;
+    if (rem >= p) rem -= p;
+    if (rem >= p) rem -= p;
+  }
   if (a.neg && rem) rem = p - rem;
   return (uint32_t)rem;
 }

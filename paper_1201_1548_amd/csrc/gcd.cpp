@@ -94,13 +94,30 @@ int write_upoly(const Poly& v, bires_upoly* out, int mem, hipStream_t st) {
   return BIRES_OK;
 }
 
-BigInt content(const Poly& v) {
-  BigInt g;
-  for (const auto& c : v) {
-    g = big_gcd(g, c);
-    if (g.mag.size() == 1 && g.mag[0] == 1u) break;
-  }
-  return g;
+// The content c >= 0 of v (0 for no coefficients), and v / c in q if given.  The
+// gcd of the outer coefficients is nearly always the content: the others are
+// divided by it, which costs one exact division each and gives the quotients;
+// only a coefficient that it does not divide costs a gcd, and then the
+// quotients a second pass.
+BigInt content(const Poly& v, Poly* q = nullptr) {
+  BigInt c;
+  if (q) q->assign(v.size(), BigInt());
+  if (v.empty()) return c;
+  c = big_gcd(v.front(), v.back());  // (the leading coefficient is not zero)
+  bool whole = true;
+  BigInt t;
+  ExactDiv d(c);
+  for (size_t i = 0; i < v.size() && !d.one(); ++i)
+    if (!d(v[i], q ? (*q)[i] : t)) {
+      whole = false;
+      c = big_gcd(c, v[i]);
+      d = ExactDiv(c);
+    }
+  if (q && d.one())
+    *q = v;
+  else if (q && !whole)
+    for (size_t i = 0; i < v.size(); ++i) (void)d(v[i], (*q)[i]);
+  return c;
 }
 
 // x with positive leading coefficient
@@ -403,10 +420,7 @@ int gcd_core(Context* cx, const Poly& A, const Poly& B, hipStream_t st, Poly& G,
     need = (int)std::ceil(std::max<double>(need, n1(rec[0]) + std::max(n1(rec[1]), n1(rec[2])) + 8.0)) * 2;
   }
   const Poly& Fs = rec[0];
-  const BigInt cf = content(Fs);
-  G.assign(Fs.size(), BigInt());
-  for (size_t i = 0; i < Fs.size(); ++i)
-    if (!big_divexact(Fs[i], cf, G[i])) return BIRES_ECHECK;
+  const BigInt cf = content(Fs, &G);
   const bool flip = G.back().neg;
   make_positive(G);
   if (G.size() == 1) {  // coprime: the cofactors are A and B
@@ -424,17 +438,13 @@ int gcd_core(Context* cx, const Poly& A, const Poly& B, hipStream_t st, Poly& G,
     const BigInt h = big_gcd(cf, lc);
     BigInt num, den;
     if (!big_divexact(cf, h, num) || !big_divexact(lc, h, den)) return BIRES_ECHECK;
-    const bool unit = den.mag.size() == 1 && den.mag[0] == 1u;
     const bool neg = den.neg != flip;
     den.neg = false;
+    ExactDiv by(den);
     C->assign(Q.size(), BigInt());
     for (size_t i = 0; i < Q.size(); ++i) {
-      const BigInt t = (num.mag.size() == 1 && num.mag[0] == 1u && !num.neg) ? Q[i] : big_mul(num, Q[i]);
-      if (unit) {
-        (*C)[i] = t;
-      } else if (!big_divexact(t, den, (*C)[i])) {
-        return BIRES_ECHECK;
-      }
+      const bool same = num.mag.size() == 1 && num.mag[0] == 1u && !num.neg;
+      if (!(same ? by(Q[i], (*C)[i]) : by(big_mul(num, Q[i]), (*C)[i]))) return BIRES_ECHECK;
       if (neg) (*C)[i].neg = !(*C)[i].neg && !(*C)[i].is_zero();
     }
     trim_poly(*C);
@@ -447,10 +457,7 @@ int gcd_core(Context* cx, const Poly& A, const Poly& B, hipStream_t st, Poly& G,
 int gcd_cofactors(Context* cx, const Poly& A, const Poly& B, hipStream_t st, Poly& G, Poly& CA, Poly& CB) {
   if (B.empty()) {
     if (A.empty()) return BIRES_EINVAL;
-    const BigInt c = content(A);
-    G.assign(A.size(), BigInt());
-    for (size_t i = 0; i < A.size(); ++i)
-      if (!big_divexact(A[i], c, G[i])) return BIRES_ECHECK;
+    const BigInt c = content(A, &G);
     BigInt u = c;
     if (G.back().neg) u.neg = true;
     make_positive(G);
@@ -477,9 +484,8 @@ Poly derivative(const Poly& v) {
 Poly poly_sub(const Poly& a, const Poly& b) {
   Poly r(std::max(a.size(), b.size()));
   for (size_t i = 0; i < r.size(); ++i) {
-    BigInt nb = i < b.size() ? b[i] : BigInt();
-    nb.neg = !nb.neg && !nb.is_zero();
-    r[i] = big_add(i < a.size() ? a[i] : BigInt(), nb);
+    if (i < a.size()) r[i] = a[i];
+    if (i < b.size()) big_sub_from(r[i], b[i]);
   }
   trim_poly(r);
   return r;
@@ -519,11 +525,10 @@ int run_squarefree(Context* cx, const bires_upoly& r, bires_upoly* unit, bires_u
   std::vector<Poly> out;
   BigInt u;  // signed content
   if (R.size() >= 2) {
-    u = content(R);
+    Poly Rp;
+    u = content(R, &Rp);
     if (R.back().neg) u.neg = true;
-    Poly Rp(R.size());
-    for (size_t i = 0; i < R.size(); ++i)
-      if (!big_divexact(R[i], u, Rp[i])) return BIRES_ECHECK;
+    make_positive(Rp);
     // Yun: b_1 = R / g, d_1 = R' / g - b_1' with g = gcd(R, R'); then
     // a_i = gcd(b_i, d_i), b_{i+1} = b_i / a_i, d_{i+1} = d_i / a_i - b_{i+1}'
     Poly g, b, c;
