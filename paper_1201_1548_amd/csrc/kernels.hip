@@ -128,12 +128,8 @@ __global__ void k_transpose(const uint32_t* src, uint32_t* dst, int rows, int co
 // ---------------------------------------------------------------------------
 // (a) reduction modulo the primes.  Each job has ceil(Tf/64) blocks for f
 // then ceil(Tg/64) for g, 64 coefficients each; blockIdx.y selects a tile of
-// KT primes.  A coefficient
-// with limbs w_0..w_{L-1} (two's complement) has value sum w_l 2^{32l} - s 2^{32L};
-// its Montgomery residue is built by Horner over the limbs with one two-product
-// reduction per limb, then the sign term (R^L)_M is subtracted.
-
-constexpr int KT = 16;
+// kt primes.  A coefficient with limbs w_0..w_{L-1} (two's complement) has value
+// sum w_l 2^{32l} - s 2^{32L}.
 
 // Local block lb of a job (64 coefficients), primes [k0, k1).
 __device__ void dev_reduce(const JobDev& J, int lb, int k0, int k1, TablesDev tab) {
@@ -197,20 +193,54 @@ __device__ void dev_reduce(const JobDev& J, int lb, int k0, int k1, TablesDev ta
     }
     return;
   }
+  // several limbs: exact sums of w_l (2^{32 l} R^2 mod p) in 96 bits for KL
+  // primes at once.  The weights are the same for every lane (the next one is a
+  // product in scalar registers), so a limb costs a lane two instructions per
+  // prime, and the KL sums are independent.  Bound by latency at few coefficients
+  // (3121 of 66 limbs, 76 primes: 73 us by Horner's rule with one reduction per
+  // limb, 16 primes in turn; 15 here), by the stores at many (the pairs of 400
+  // curves, 1 to 2 limbs: 417 and 354 us).
   const bool negv = (src[L - 1] >> 31) != 0u;
-  for (int k = k0; k < k1; ++k) {
-    const ModP q = tab.primes[k];
-    uint32_t x = 0;
-    for (int l = L - 1; l >= 0; --l) x = mdot2(x, q.r2, reduce32(src[l], q.p), q.r2, q);
-    if (negv) x = msub(x, mpow(q.r2, (uint32_t)L, q), q.p);
-    if (mult) x = mmul(x, to_mont(mult, q), q);
-    dst[(size_t)k * T] = J.dig ? digits4(x, q.p) : x;
+  constexpr int KL = 4;
+  for (int kb = k0; kb < k1; kb += KL) {
+    uint64_t lo[KL];
+    uint32_t hi[KL], c[KL];
+    ModP q[KL];
+#pragma unroll
+    for (int j = 0; j < KL; ++j) {
+      q[j] = tab.primes[min(kb + j, k1 - 1)];
+      lo[j] = 0;
+      hi[j] = 0u;
+      c[j] = q[j].r2;
+    }
+#pragma unroll 4
+    for (int l = 0; l < L; ++l) {
+      const uint32_t w = src[l];
+#pragma unroll
+      for (int j = 0; j < KL; ++j) {
+        const uint64_t t = (uint64_t)w * c[j];
+        lo[j] += t;
+        hi[j] += lo[j] < t ? 1u : 0u;
+        c[j] = mmul(c[j], q[j].r2, q[j]);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < KL; ++j) {
+      if (kb + j >= k1) break;
+      Acc96 A;
+      A.lo = lo[j];
+      A.hi = hi[j];
+      uint32_t x = fold96(A, q[j]);
+      if (negv) x = msub(x, from_mont(c[j], q[j]), q[j].p);  // c = 2^{32 L} R^2
+      if (mult) x = mmul(x, to_mont(mult, q[j]), q[j]);
+      dst[(size_t)(kb + j) * T] = J.dig ? digits4(x, q[j].p) : x;
+    }
   }
 }
 
-__global__ void k_reduce(const JobDev* jobs, const int* starts, int nj, TablesDev tab) {
+__global__ void k_reduce(const JobDev* jobs, const int* starts, int nj, int kt, TablesDev tab) {
   const int job = find_job(starts, nj, blockIdx.x, gridDim.x);
-  dev_reduce(jobs[job], blockIdx.x - starts[job], blockIdx.y * KT, blockIdx.y * KT + KT, tab);
+  dev_reduce(jobs[job], blockIdx.x - starts[job], blockIdx.y * kt, blockIdx.y * kt + kt, tab);
 }
 
 // ---------------------------------------------------------------------------
@@ -2595,8 +2625,11 @@ void launch_transpose(const uint32_t* src, uint32_t* dst, int rows, int cols, in
 
 void launch_reduce(const JobDev* jobs, const int* starts, int nj, int nblocks, int max_primes, TablesDev tab,
                    hipStream_t s) {
-  dim3 grid(nblocks, (max_primes + KT - 1) / KT);
-  hipLaunchKernelGGL(k_reduce, grid, dim3(64), 0, s, jobs, starts, nj, tab);
+  // 16 primes per block share the limbs' loads (and the prime constants come in
+  // eights); below two waves per SIMD at that split, blocks of 4 primes fill the chip
+  const int kt = (long)nblocks * ((max_primes + 15) / 16) < 2048 ? 4 : 16;
+  dim3 grid(nblocks, (max_primes + kt - 1) / kt);
+  hipLaunchKernelGGL(k_reduce, grid, dim3(64), 0, s, jobs, starts, nj, kt, tab);
 }
 
 int eval_elim_block() { return 64; }
