@@ -24,6 +24,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstdlib>
 #include <type_traits>
 #include <utility>
 
@@ -387,7 +388,12 @@ __device__ __forceinline__ void ee_first(int32_t (&X)[C], int32_t (&Y)[C], int a
 #undef EE_SET
 #undef EE_OWN
 
-// In the chain A is X at even degrees of the divisor.
+// The normal remainder sequence from a divisor of degree bs >= 1 down to a
+// constant remainder, which is left in Y[0].  A is X at even degrees of the divisor;
+// a0: A's balanced leading coefficient.  post(bs, l2, lead) is called after
+// every step with the divisor's degree and the remainder's leading coefficient.
+// Returns false (on every lane) when a divisor's leading coefficient vanishes at
+// some lane's point.
 #define EE_CHAIN_STEP(BV)                                                  \
   if constexpr (BV <= CH && BV + 1 < C) {                                  \
     if (bs >= BV) {                                                        \
@@ -395,34 +401,46 @@ __device__ __forceinline__ void ee_first(int32_t (&X)[C], int32_t (&Y)[C], int a
       if (__ballot(lb == 0) != 0ull) return false;                         \
       const int32_t l2 = ee_step<C, BV, ((BV) & 1) == 0>(X, Y, a0, lb, q); \
       a0 = lb;                                                             \
-      pfx = smul(pfx, l2, q);                                              \
-      if (BV > 1) den = smul(den, pfx, q);                                 \
+      post(BV, l2, ((BV) & 1) ? Y[0] : X[0]);                              \
     }                                                                      \
   }
-
 #define EE_ANY_STEP(AX)                                             \
   {                                                                 \
     const int32_t lb = balance(AX ? Y[0] : X[0], q.p);              \
     if (__ballot(lb == 0) != 0ull) return false;                    \
     const int32_t l2 = ee_step_any<C, CH, AX>(X, Y, bs, a0, lb, q); \
     a0 = lb;                                                        \
-    pfx = smul(pfx, l2, q);                                         \
-    den = smul(den, pfx, q);                                        \
+    post(bs, l2, AX ? X[0] : Y[0]);                                 \
     bs -= 1;                                                        \
   }
+template <int C, int CH, class F>
+__device__ __forceinline__ bool ee_chain(int32_t (&X)[C], int32_t (&Y)[C], int bs, int32_t a0, const SModP& q, F post) {
+  if constexpr (C > CH) {
+    // pairs of an even and an odd step; an odd start skips the first even one
+    // (conditional updates in place, not the two arms of a branch that merge)
+    int skip = bs & 1;
+    while (bs > CH) {
+      asm("" : "+s"(skip));
+      if (!skip) EE_ANY_STEP(true)
+      skip = 0;
+      EE_ANY_STEP(false)
+    }
+  }
+  EE_CHAIN_STEP(30) EE_CHAIN_STEP(29) EE_CHAIN_STEP(28) EE_CHAIN_STEP(27) EE_CHAIN_STEP(26) EE_CHAIN_STEP(25)
+  EE_CHAIN_STEP(24) EE_CHAIN_STEP(23) EE_CHAIN_STEP(22) EE_CHAIN_STEP(21) EE_CHAIN_STEP(20) EE_CHAIN_STEP(19)
+  EE_CHAIN_STEP(18) EE_CHAIN_STEP(17) EE_CHAIN_STEP(16) EE_CHAIN_STEP(15) EE_CHAIN_STEP(14) EE_CHAIN_STEP(13)
+  EE_CHAIN_STEP(12) EE_CHAIN_STEP(11) EE_CHAIN_STEP(10) EE_CHAIN_STEP(9) EE_CHAIN_STEP(8) EE_CHAIN_STEP(7)
+  EE_CHAIN_STEP(6) EE_CHAIN_STEP(5) EE_CHAIN_STEP(4) EE_CHAIN_STEP(3) EE_CHAIN_STEP(2) EE_CHAIN_STEP(1)
+  return true;
+}
+#undef EE_CHAIN_STEP
+#undef EE_ANY_STEP
 
-// Returns false (on every lane) when the block must be recomputed by
-// dev_eval_elim: a leading coefficient vanishes at some lane's point, or a
-// remainder is shorter than a normal sequence's.  Needs 1 <= m, n < C.
-template <int C, int CH, int KW>
-__device__ __forceinline__ bool dev_ee(const JobDev& J, int lb_, TablesDev tab, int8_t* planes) {
-  const int nbpp = (J.D + 63) / 64;
-  const int k = lb_ / nbpp;
-  const int l = lane_id();
-  const int pt = (lb_ - k * nbpp) * 64 + l;
-  const int m = J.m, n = J.n;
-  const SModP q(tab.primes[k]);
-  EvalCtx E;
+// The values of f and g at the block's points: of f in X if xf, else in Y.
+template <int C, int KW>
+__device__ __forceinline__ void ee_eval(const JobDev& J, int k, int pt, TablesDev tab, int8_t* planes, bool xf,
+                                        EvalCtx& E, int32_t (&X)[C], int32_t (&Y)[C], const SModP& q) {
+  const int l = lane_id(), m = J.m, n = J.n;
   E.planes = planes;
   E.dmax = max(J.ldf, J.kind ? J.ldf : J.ldg) - 1;
   E.one = balance((int32_t)q.one, q.p);
@@ -464,20 +482,12 @@ __device__ __forceinline__ bool dev_ee(const JobDev& J, int lb_, TablesDev tab, 
     if (E.dmax >= KW) E.apw = balance(w[0], q.p);
   }
   group_sync<true>();
-  // the operand of larger degree (A) and the other; which register array
-  // holds A: at the start of the chain A is X when the divisor's degree is even
-  const bool sw = m < n;
-  const int as0 = sw ? n : m, bs0 = sw ? m : n;
-  const bool normal = as0 == bs0 + 1;
-  const bool ax = normal ? (bs0 & 1) == 0 : ((bs0 - 1) & 1) != 0;
-  const bool xf = ax != sw;  // X holds f
   const uint32_t* Rf = J.res_f + (size_t)k * J.Tf;
   const uint32_t* Rg = J.res_g + (size_t)k * J.Tg;
   // One copy of the tile code for all row tiles (unrolled it would overflow
   // the instruction cache); each tile's values are moved to their registers
   // behind a scalar branch.
   constexpr int T = (C + 15) / 16;
-  int32_t X[C], Y[C];
   sfor<C>(EE_IDX(i) { X[i] = Y[i] = own_reg(0); });  // (opaque zeros: a fill would keep the array whole)
 #pragma unroll 1
   for (int w = 0; w < 2; ++w) {
@@ -496,6 +506,28 @@ __device__ __forceinline__ bool dev_ee(const JobDev& J, int lb_, TablesDev tab, 
       });
     }
   }
+}
+
+// Returns false (on every lane) when the block must be recomputed by
+// dev_eval_elim: a leading coefficient vanishes at some lane's point, or a
+// remainder is shorter than a normal sequence's.  Needs 1 <= m, n < C.
+template <int C, int CH, int KW>
+__device__ __forceinline__ bool dev_ee(const JobDev& J, int lb_, TablesDev tab, int8_t* planes) {
+  const int nbpp = (J.D + 63) / 64;
+  const int k = lb_ / nbpp;
+  const int pt = (lb_ - k * nbpp) * 64 + lane_id();
+  const int m = J.m, n = J.n;
+  const SModP q(tab.primes[k]);
+  // the operand of larger degree (A) and the other; which register array
+  // holds A: at the start of the chain A is X when the divisor's degree is even
+  const bool sw = m < n;
+  const int as0 = sw ? n : m, bs0 = sw ? m : n;
+  const bool normal = as0 == bs0 + 1;
+  const bool ax = normal ? (bs0 & 1) == 0 : ((bs0 - 1) & 1) != 0;
+  const bool xf = ax != sw;  // X holds f
+  EvalCtx E;
+  int32_t X[C], Y[C];
+  ee_eval<C, KW>(J, k, pt, tab, planes, xf, E, X, Y, q);
   int as = as0, bs = bs0;
   bool neg = sw && ((m * n) & 1);
   int32_t num = E.one, den = E.one, pfx = E.one;
@@ -524,22 +556,11 @@ __device__ __forceinline__ bool dev_ee(const JobDev& J, int lb_, TablesDev tab, 
       bs -= 1;
     }
   }
-  if constexpr (C > CH) {
-    // pairs of an even and an odd step; an odd start skips the first even one
-    // (conditional updates in place, not the two arms of a branch that merge)
-    int skip = bs & 1;
-    while (bs > CH) {
-      asm("" : "+s"(skip));
-      if (!skip) EE_ANY_STEP(true)
-      skip = 0;
-      EE_ANY_STEP(false)
-    }
-  }
-  EE_CHAIN_STEP(30) EE_CHAIN_STEP(29) EE_CHAIN_STEP(28) EE_CHAIN_STEP(27) EE_CHAIN_STEP(26) EE_CHAIN_STEP(25)
-  EE_CHAIN_STEP(24) EE_CHAIN_STEP(23) EE_CHAIN_STEP(22) EE_CHAIN_STEP(21) EE_CHAIN_STEP(20) EE_CHAIN_STEP(19)
-  EE_CHAIN_STEP(18) EE_CHAIN_STEP(17) EE_CHAIN_STEP(16) EE_CHAIN_STEP(15) EE_CHAIN_STEP(14) EE_CHAIN_STEP(13)
-  EE_CHAIN_STEP(12) EE_CHAIN_STEP(11) EE_CHAIN_STEP(10) EE_CHAIN_STEP(9) EE_CHAIN_STEP(8) EE_CHAIN_STEP(7)
-  EE_CHAIN_STEP(6) EE_CHAIN_STEP(5) EE_CHAIN_STEP(4) EE_CHAIN_STEP(3) EE_CHAIN_STEP(2) EE_CHAIN_STEP(1)
+  if (!ee_chain<C, CH>(X, Y, bs, a0, q, [&](int b, int32_t l2, int32_t) __attribute__((always_inline)) {
+        pfx = smul(pfx, l2, q);
+        if (b > 1) den = smul(den, pfx, q);
+      }))
+    return false;
   // the constant remainder: degree 0 is even, so A (degree 1) is X and it is in Y
   const int32_t last = balance(Y[0], q.p);
   if (__ballot(last == 0) != 0ull) return false;
@@ -590,6 +611,99 @@ BIRES_EE_KERNEL(24, 30, 32, 4)
 BIRES_EE_KERNEL(32, 30, 32, 3)
 BIRES_EE_KERNEL(48, 22, 64, 2)
 BIRES_EE_KERNEL(68, 22, 64, 2)
+
+// Principal subresultant coefficients sr_i(a), i < K, of degrees that differ by at
+// most one: psc_lane's recurrence along the normal sequence, whose steps all
+// multiply by lc(B)^2 = l2 (equal degrees: a first one by lc(B)).  nm, dn: LDS [K][64]
+// numerators and denominators of the block's points, inverted together at
+// the end.  Returns false when a formal or actual leading coefficient vanishes
+// at some lane's point (the general kernel then does the block).
+template <int C, int CH, int KW>
+__device__ __forceinline__ bool dev_psc(const JobDev& J, int blk, TablesDev tab, int8_t* planes, int32_t* nm,
+                                        int32_t* dn, uint32_t* out, int K) {
+  const int l = lane_id(), pt = blk * 64 + l;
+  const int m = J.m, n = J.n;
+  const SModP q(tab.primes[0]);
+  const bool sw = m < n, eq = m == n;
+  const int bs0 = sw ? m : n;
+  const bool ax = eq ? ((bs0 - 1) & 1) != 0 : (bs0 & 1) == 0;
+  EvalCtx E;
+  int32_t X[C], Y[C];
+  ee_eval<C, KW>(J, 0, pt, tab, planes, ax != sw, E, X, Y, q);
+  int32_t a0 = balance(sel(ax, X[0], Y[0]), q.p);
+  const int32_t b0 = balance(sel(ax, Y[0], X[0]), q.p);
+  if (__ballot(a0 == 0 || b0 == 0) != 0ull) return false;
+  int E0 = sw ? (m * n) & 1 : 0, E1 = sw ? (m + n + 1) & 1 : 0;
+  int32_t Nn = E.one, Nd = E.one, sA = E.one, sB = E.one;
+  auto emit = [&](int i, int32_t vn, int32_t vd) __attribute__((always_inline)) {
+    if (i >= K) return;
+    const int32_t x = smul(Nn, vn, q);
+    nm[i * 64 + l] = ((E0 ^ (i & E1)) & 1) ? -x : x;
+    dn[i * 64 + l] = smul(Nd, vd, q);
+  };
+  int bs = bs0;
+  if (eq) {
+    int fx = ax, fy = !ax;
+    asm("" : "+s"(fx), "+s"(fy));
+    if (fx) ee_first<C, true>(X, Y, bs, bs, b0, E.one, q);
+    if (fy) ee_first<C, false>(X, Y, bs, bs, b0, E.one, q);
+    E0 ^= bs & 1;
+    E1 ^= 1;
+    Nn = b0;
+    emit(bs - 1, sel(ax, X[0], Y[0]), b0);
+    sB = b0;
+    a0 = b0;
+    bs -= 1;
+  } else if (bs0 < K) {
+    nm[bs0 * 64 + l] = b0;  // lc(B)^(a - b)
+    dn[bs0 * 64 + l] = E.one;
+  }
+  if (!ee_chain<C, CH>(X, Y, bs, a0, q, [&](int b, int32_t l2, int32_t lead) __attribute__((always_inline)) {
+        Nn = smul(Nn, l2, q);
+        Nd = smul(smul(Nd, sB, q), sB, q);
+        const int32_t sR = smul(l2, sA, q);
+        emit(b - 1, lead, sR);
+        sA = sB;
+        sB = sR;
+      }))
+    return false;
+  int32_t pre = E.one;
+#pragma unroll 4
+  for (int i = 0; i < K; ++i) {
+    nm[i * 64 + l] = smul(nm[i * 64 + l], pre, q);
+    pre = smul(pre, dn[i * 64 + l], q);
+  }
+  int32_t inv = spow(balance(pre, q.p), q.p - 2u, q);
+#pragma unroll 4
+  for (int i = K - 1; i >= 0; --i) {
+    const int32_t r = redc_s((int64_t)smul(nm[i * 64 + l], inv, q), q);
+    inv = smul(inv, dn[i * 64 + l], q);
+    if (pt < J.D) out[(size_t)i * J.D + pt] = umin32((uint32_t)r, (uint32_t)r + q.p);
+  }
+  return true;
+}
+
+// One wave per 64 points: a run has few blocks (25 at 1561 points), so latency
+// counts, and registers serve it better than arrays in LDS (k_psc): 146 -> 42 us
+// for the 40 indices of a degree-40 curve and its derivative.  One capacity: at a
+// wave per CU the zeros of a smaller job cost less than more code would.
+constexpr int PSC_CAPACITY = 68;
+__global__ __launch_bounds__(64) void k_psc_ee(JobDev J, TablesDev tab, uint32_t* out, int K, int* fallback) {
+  __shared__ __align__(16) int8_t planes[4 * 64 * 64];
+  __shared__ int32_t nm[PSC_CAPACITY * 64], dn[PSC_CAPACITY * 64];
+  const bool ok = dev_psc<PSC_CAPACITY, 22, 64>(J, blockIdx.x, tab, planes, nm, dn, out, K);
+  if (threadIdx.x == 0) fallback[blockIdx.x] = !ok;
+}
+
+// Degrees that differ by at most one are the discriminant's and Q's; a larger gap
+// would need the powers of psc_lane.
+bool psc_registers(int m, int n) {
+  return std::min(m, n) >= 1 && std::max(m, n) < PSC_CAPACITY && std::abs(m - n) <= 1;
+}
+
+void launch_psc_ee(const JobDev& J, TablesDev tab, uint32_t* out, int K, int* fallback, hipStream_t s) {
+  hipLaunchKernelGGL(k_psc_ee, dim3((J.D + 63) / 64), dim3(64), 0, s, J, tab, out, K, fallback);
+}
 
 // The smallest capacity that holds both arrays: fewer registers per lane, more
 // waves (degree 22 in the kernel of capacity 32: 3 waves instead of 4).  From 68

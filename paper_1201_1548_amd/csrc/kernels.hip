@@ -1046,22 +1046,30 @@ __device__ void psc_lane(uint32_t* A, uint32_t* B, int m, int n, int pt, int D, 
 
 // One block of W lanes = W consecutive points; prime index 0 of tab (the
 // caller passes the table shifted to its prime).  LDS: (m + n + 2) W words.
-template <int W>
-__global__ __launch_bounds__(W) void k_psc(JobDev J, TablesDev tab, PscOut o) {
+// FB: only the blocks that k_psc_ee left (residues as digit words).
+template <int W, bool FB>
+__global__ __launch_bounds__(W) void k_psc(JobDev J, TablesDev tab, PscOut o, const int* fallback) {
   extern __shared__ __align__(16) uint32_t lds[];
+  if (FB && !fallback[blockIdx.x]) return;
   const int pt = blockIdx.x * W + (int)threadIdx.x;
   if (pt >= J.D) return;
   uint32_t* A = lds + threadIdx.x;
   uint32_t* B = A + (J.m + 1) * W;
   const ModP q = tab.primes[0];
-  eval_pair<W, true>(J, 0, eval_point(tab, 0, pt, q), q, A, B);
+  eval_pair<W, true, FB>(J, 0, eval_point(tab, 0, pt, q), q, A, B);
   psc_lane<W>(A, B, J.m, J.n, pt, J.D, q, o);
 }
 
-void launch_psc(const JobDev& J, TablesDev tab, uint32_t* num, uint32_t* den, int K, hipStream_t s) {
+void launch_psc(const JobDev& J, TablesDev tab, uint32_t* num, uint32_t* den, int K, int* fallback, hipStream_t s) {
   const PscOut o{num, den, K};
   const size_t lds = (size_t)(J.m + J.n + 2) * 64 * sizeof(uint32_t);
-  hipLaunchKernelGGL(k_psc<64>, dim3((J.D + 63) / 64), dim3(64), lds, s, J, tab, o);
+  const dim3 grid((J.D + 63) / 64);
+  if (J.dig) {
+    launch_psc_ee(J, tab, num, K, fallback, s);
+    hipLaunchKernelGGL((k_psc<64, true>), grid, dim3(64), lds, s, J, tab, o, fallback);
+  } else {
+    hipLaunchKernelGGL((k_psc<64, false>), grid, dim3(64), lds, s, J, tab, o, nullptr);
+  }
 }
 
 size_t psc_lds_bytes(int m, int n) { return (size_t)(m + n + 2) * 64 * sizeof(uint32_t); }

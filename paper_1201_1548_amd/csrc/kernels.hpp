@@ -152,7 +152,11 @@ void launch_fused(int C, int KS, const FusedPlan& F, size_t lds_bytes, int block
 // formal degrees; writes sr_i(a) (plain) to num[i * D + a] for i < K, with
 // den ([K][D]) as workspace.
 size_t psc_lds_bytes(int m, int n);
-void launch_psc(const JobDev& J, TablesDev tab, uint32_t* num, uint32_t* den, int K, hipStream_t s);
+// J.dig = psc_registers(m, n): in registers (ee.hip; fallback: one int per 64
+// points), the blocks it leaves and all others with the arrays in LDS.
+bool psc_registers(int m, int n);
+void launch_psc(const JobDev& J, TablesDev tab, uint32_t* num, uint32_t* den, int K, int* fallback, hipStream_t s);
+void launch_psc_ee(const JobDev& J, TablesDev tab, uint32_t* out, int K, int* fallback, hipStream_t s);
 // The N^- / N^+ degree chain over prime index 0 of tab, two blocks (the second
 // buffers of the gcds only where lds_per_block has room for them).
 size_t fiber_chain_lds_bytes(int dr, int D, int Dq);

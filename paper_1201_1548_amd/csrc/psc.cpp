@@ -93,10 +93,19 @@ TablesDev shifted(const TablesDev& t, int k) {
 
 // The psc's of one planned job on the device: coefficients [K][D] (plain) at
 // *coefs inside `ws`, which the caller keeps.
+// The work is queued on the stream: the buffers go back to their pools after it.
 struct PscRun {
-  DevBuf ws;
+  struct Queued {
+    hipStream_t st = nullptr;
+    bool on = false;
+    ~Queued() {
+      if (on) (void)hipStreamSynchronize(st);
+    }
+  };
+  DevBuf ws, host;
   const uint32_t* coefs = nullptr;
   int K = 0, D = 0, m = -1, n = -1;
+  Queued queued;  // (the last member: waits before the buffers go)
 };
 
 }  // namespace
@@ -132,16 +141,16 @@ static int psc_device(Context* cx, const HostJob& h, int kind, int kp, int kmax,
   const size_t o_ij = L.take(sizeof(JobDev) * K);
   const size_t o_is = L.take(sizeof(int) * (K + 1));
   const size_t up_end = L.bytes;
-  const size_t o_rf = L.take((size_t)Tf * 4 + 256);  // whole-chunk loads read past a short row
-  const size_t o_rg = L.take((size_t)Tg * 4 + 256);
+  const size_t o_rf = L.take((size_t)Tf * 4 + EE_SLACK_BYTES);  // whole-chunk loads read past a short row
+  const size_t o_rg = L.take((size_t)Tg * 4 + EE_SLACK_BYTES);
+  const size_t o_fb = L.take((size_t)((D + 63) / 64) * sizeof(int));
   const size_t o_num = L.take((size_t)K * D * 4);
   const size_t o_den = L.take((size_t)K * D * 4);
   const size_t o_co = L.take((size_t)K * D * 4);
   r.ws.take(&cx->dev, L.bytes);
-  DevBuf host;
-  host.take(&cx->host, up_end);
-  if (!r.ws.p || !host.p) return BIRES_ENOMEM;
-  uint8_t* H = host.as<uint8_t>();
+  r.host.take(&cx->host, up_end);
+  if (!r.ws.p || !r.host.p) return BIRES_ENOMEM;
+  uint8_t* H = r.host.as<uint8_t>();
   std::memset(H, 0, up_end);
   std::memcpy(H + o_lf, h.f.data(), h.f.size() * 4);
   if (!h.g.empty()) std::memcpy(H + o_lg, h.g.data(), h.g.size() * 4);
@@ -168,6 +177,7 @@ static int psc_device(Context* cx, const HostJob& h, int kind, int kp, int kmax,
   J.rowdeg_g = r.ws.as<int32_t>(o_rd) + pl.m + 1;
   J.res_f = r.ws.as<uint32_t>(o_rf);
   J.res_g = r.ws.as<uint32_t>(o_rg);
+  J.dig = psc_registers(pl.m, pl.n);
   std::memcpy(H + o_job, &J, sizeof J);
   int* st2 = (int*)(H + o_st);
   st2[0] = 0;
@@ -186,16 +196,16 @@ static int psc_device(Context* cx, const HostJob& h, int kind, int kp, int kmax,
   TablesDev base = cx->tab;
   const bool geo = geo_tables_device(cx, D, kp + 1, st, &base);
   const TablesDev tab = shifted(base, kp);
+  r.queued.st = st;
+  r.queued.on = true;
   DEV(hipMemcpyAsync(r.ws.p, H, up_end, hipMemcpyHostToDevice, st));
   launch_reduce(r.ws.as<JobDev>(o_job), r.ws.as<int>(o_st), 1, st2[1], 1, tab, st);
-  launch_psc(J, tab, r.ws.as<uint32_t>(o_num), r.ws.as<uint32_t>(o_den), K, st);
+  launch_psc(J, tab, r.ws.as<uint32_t>(o_num), r.ws.as<uint32_t>(o_den), K, r.ws.as<int>(o_fb), st);
   if (geo)
     launch_interp_geo(geo_class(D), r.ws.as<JobDev>(o_ij), r.ws.as<int>(o_is), K, K, D, tab, st);
   else
     launch_interp(r.ws.as<JobDev>(o_ij), r.ws.as<int>(o_is), K, K, D, tab, nullptr, nullptr, 0, st);
   DEV(hipGetLastError());
-  // the staging block is read by the copy: it must outlive it
-  DEV(hipStreamSynchronize(st));
   r.coefs = r.ws.as<uint32_t>(o_co);
   return BIRES_OK;
 }
