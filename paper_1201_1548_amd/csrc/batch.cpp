@@ -1158,7 +1158,13 @@ int run_batch_finish(PendingPtr P) {
               SpecJob{x.status, x.active, x.pl, x.Lout, x.degcap, x.Tf, x.Tg, x.ldg, x.Lacc, P->rd_off[i]};
         }
         sc.rowdeg = P->rowdeg;
-        // a fresh device copy: calls in flight keep the one they check against
+        sc.dimg = nullptr;
+        sc.valid = true;
+      } else if (!sc.dimg) {
+        // The statistics have repeated: the next call may plan by them and check
+        // them on the device.  Only now, since the allocation, the copy and
+        // the release of the previous image cost 85 us, which calls on changing
+        // inputs would pay every time.  (Calls in flight keep the image they check against.)
         std::shared_ptr<DevImage> di = std::make_shared<DevImage>();
         bool up = hipMalloc((void**)&di->d, scan_words * 4) == hipSuccess;
         if (!up) di->d = nullptr;
