@@ -650,6 +650,15 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
     itW = itQ = nullptr;
     itNB = 0;
   }
+  // the powers of the points, for launches that fill the chip: below two blocks
+  // per SIMD the evaluation computes them in the time that they take to arrive
+  if (!debug && !noalloc && !fused && !schur && starts[K_RG0][nj] + starts[K_RG0 + 1][nj] >= 2048) {
+    int rD = 0, rP = 0;
+    for (int i = 0; i < nj; ++i)
+      if (starts[K_RG0][i + 1] != starts[K_RG0][i] || starts[K_RG0 + 1][i + 1] != starts[K_RG0 + 1][i])
+        rD = std::max(rD, w[i].pl.D), rP = std::max(rP, w[i].pl.P);
+    pow_planes_device(cx, rD, rP, st, &etab);
+  }
   const int gDp = (gD + 31) & ~31, gNp = ((int)group.size() + 31) & ~31;
   const size_t o_yp = group.empty() ? 0 : ws.take((size_t)4 * gNp * gDp * gP);
   // persistent fused launch: the evaluation's block lists (register Euclid at

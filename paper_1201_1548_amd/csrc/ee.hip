@@ -46,6 +46,13 @@ struct SModP : ModP {
   __device__ __forceinline__ explicit SModP(const ModP& q) : ModP(q), pin(0u - q.pinv) { asm("" : "+s"(pin)); }
 };
 
+// A copy whose p is opaque, for the code of one block: as a factor p is sign-extended,
+// and an extension shared between blocks is multiplied as a 64-bit number.
+__device__ __forceinline__ SModP own_mod(SModP q) {
+  asm("" : "+s"(q.p));
+  return q;
+}
+
 // t 2^{-32} mod p.  redc_s takes the low words' equality out of the difference:
 // with m = t p^{-1} mod 2^32, t - m p has a zero low word, so its high word is
 // hi(t) - mulhi(m, p), a 32-bit result of its own.  redc_p is one multiply-add,
@@ -140,22 +147,46 @@ struct EvalCtx {
   int dmax;              // largest x-degree
 };
 
-// Rows 16 tau .. 16 tau + 15 (top-aligned: row k holds y^(deg - k)) of one
-// operand at the block's points: out[i] = the value of row 16 tau + i at this
-// lane's point, zero past the degree.  Row slot rho of the matrix tile holds
-// row 4 (rho % 4) + rho / 4, so that register j of lane group g is row 4 j + g:
-// the slots past the degree are whole registers and their epilogue is skipped.
-template <int KW>
-__device__ __forceinline__ void eval_tile(const uint32_t* rows, const int32_t* rowdeg, int lp, int deg, int tau,
-                                          const EvalCtx& E, int32_t (&out)[16], const SModP& q) {
+// The rows of one operand, top-aligned: row k holds y^(deg - k).
+struct Rows {
+  const uint32_t* r;
+  const int32_t* deg_x;
+  int lp, deg;
+};
+
+// A tile of 16 rows at the block's points; out[i]: this lane's value of the
+// tile's row i, zero past the degree.  Rows base .. base + 15 of x (which = 0) or
+// of y (1), or (2) the 4 RJ rows from base on of x and then as many of y.  Row
+// slot rho of the matrix tile holds row 4 (rho % 4) + rho / 4, so that register j
+// of lane group g is row 4 j + g: the slots past the degree are whole registers
+// and their epilogue is skipped.
+template <int KW, int RJ>
+__device__ __forceinline__ void eval_tile(const Rows& x, const Rows& y, int which, int base, const EvalCtx& E,
+                                          int32_t (&out)[16], const SModP& q0) {
   typedef Oper<KW> OP;
   constexpr int NQ = KW / 16;  // quads of coefficients per lane
   const int l = lane_id(), rho = l & 15, g = l >> 4;
-  const int k = 16 * tau + 4 * (rho & 3) + (rho >> 2);
+  int jr = rho & 3;
+  bool isy = which == 1, past = false;
+  int live = 0;  // registers with rows up to the degree
+  if (which == 2) {
+    isy = jr >= RJ;
+    past = jr >= 2 * RJ;
+    jr = isy ? jr - RJ : jr;
+#pragma unroll
+    for (int j = 0; j < 2 * RJ; ++j)
+      live |= base + 4 * (j % RJ) <= (j < RJ ? x.deg : y.deg) ? 1 << j : 0;
+  } else {
+    const int d = which ? y.deg : x.deg;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) live |= base + 4 * j <= d ? 1 << j : 0;
+  }
+  const int k = base + 4 * jr + (rho >> 2), deg = isy ? y.deg : x.deg, lp = isy ? y.lp : x.lp;
+  const uint32_t* rows = isy ? y.r : x.r;
   const int row = max(deg - k, 0);
-  const bool past = k > deg;
+  past |= k > deg;
   const bool longrows = E.dmax >= KW;
-  const int rd = longrows ? rowdeg[row] : 0;
+  const int rd = longrows ? (isy ? y.deg_x : x.deg_x)[row] : 0;
   bool first = true;
   for (int ch = longrows ? E.dmax / KW : 0; ch >= 0; --ch) {
     if (longrows && first && ch && __ballot(!past && rd >= ch * KW) == 0ull) continue;
@@ -174,6 +205,8 @@ __device__ __forceinline__ void eval_tile(const uint32_t* rows, const int32_t* r
     typename OP::T a[4];
 #pragma unroll
     for (int s = 0; s < 4; ++s) a[s] = OP::pack(pl[s]);
+    int32_t w16 = 65536;  // (opaque: as a constant it becomes 64-bit shifts and additions)
+    asm("" : "+s"(w16));
     int32_t u[4][4];  // [point tile][register]
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
@@ -193,18 +226,20 @@ __device__ __forceinline__ void eval_tile(const uint32_t* rows, const int32_t* r
       // balanced weights of 2^32 and 2^48 stays below 2^59
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        if (16 * tau + 4 * j <= deg) {
+        if (live >> j & 1) {
+          const SModP q = own_mod(q0);
           const int32_t A = G[0][j] + (G[1][j] << 8), B = G[2][j] + (G[3][j] << 8), Cc = G[4][j] + (G[5][j] << 8);
           // (no inline assembly on the accumulators: the compiler counts the wait
           // states between a matrix product and a reader of its result only
           // for instructions it knows)
-          const int64_t s = (int64_t)A + (int64_t)B * 65536 + (int64_t)Cc * E.w32 + (int64_t)G[6][j] * E.w48;
+          const int64_t s = mad_s(G[6][j], E.w48, mad_s(Cc, E.w32, mad_s(B, w16, A)));
           u[t][j] = redc_s(s, q);
         } else {
           u[t][j] = 0;
         }
       }
     }
+    const SModP q = own_mod(q0);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       // lane row g' receives from the tile of its own points
@@ -284,9 +319,10 @@ __device__ __forceinline__ SStep ee_consts(const int32_t (&X)[C], const int32_t 
 
 // The step for the degree B of the divisor known at compile time.
 template <int C, int B, bool AX>
-__device__ __forceinline__ int32_t ee_step(int32_t (&X)[C], int32_t (&Y)[C], int32_t a0, int32_t lb, const SModP& q) {
+__device__ __forceinline__ int32_t ee_step(int32_t (&X)[C], int32_t (&Y)[C], int32_t a0, int32_t lb, const SModP& q0) {
   static_assert(B >= 1 && B + 1 < C, "A of degree B + 1 must fit");
   __builtin_amdgcn_sched_barrier(0);
+  const SModP q = own_mod(q0);
   sfor<B + 2>(EE_IDX(k) { EE_OWN(k); });
   const SStep c = ee_consts<C, AX>(X, Y, a0, lb, q);
   sfor<B - 1>(EE_IDX(k) { EE_SET(k, sdot3<AX>(c.l2, EE_A(k + 2), c.l1, EE_B(k + 2), c.n2, EE_B(k + 1), q)); });
@@ -307,15 +343,16 @@ __device__ __forceinline__ uint32_t block_mask(int n) {
 // which leaves zeros past the remainder's.
 template <int C, int CH, bool AX>
 __device__ __forceinline__ int32_t ee_step_any(int32_t (&X)[C], int32_t (&Y)[C], int bs, int32_t a0, int32_t lb,
-                                               const SModP& q) {
+                                               const SModP& q0) {
   static_assert(C % 4 == 0, "blocks of four");
   const uint32_t msk = block_mask(bs + 2);
   EE_OWN(1);
-  const SStep c = ee_consts<C, AX>(X, Y, a0, lb, q);
+  const SStep c = ee_consts<C, AX>(X, Y, a0, lb, own_mod(q0));
   sfor<C / 4>(EE_IDX(blk) {
     constexpr int k0 = 4 * blk;
     if (k0 < CH + 3 || (msk >> blk & 1u)) {
       __builtin_amdgcn_sched_barrier(0);
+      const SModP q = own_mod(q0);
       sfor<6>(EE_IDX(i) {
         if constexpr (k0 + i < C) EE_OWN(k0 + i);
       });
@@ -339,12 +376,13 @@ __device__ __forceinline__ int32_t ee_step_any(int32_t (&X)[C], int32_t (&Y)[C],
 // and A's zeros when the degrees are equal.
 template <int C, bool AX>
 __device__ __forceinline__ void ee_elim(int32_t (&X)[C], int32_t (&Y)[C], int bs, int32_t x, int32_t y,
-                                        const SModP& q) {
+                                        const SModP& q0) {
   const uint32_t msk = block_mask(bs);
   sfor<C / 4>(EE_IDX(blk) {
     constexpr int j0 = 4 * blk;
     if (msk >> blk & 1u) {
       __builtin_amdgcn_sched_barrier(0);
+      const SModP q = own_mod(q0);
       sfor<5>(EE_IDX(i) {
         if constexpr (j0 + i < C) EE_OWN(j0 + i);
       });
@@ -436,74 +474,96 @@ __device__ __forceinline__ bool ee_chain(int32_t (&X)[C], int32_t (&Y)[C], int b
 #undef EE_CHAIN_STEP
 #undef EE_ANY_STEP
 
+// Digit planes [4][64][KW] of the powers 0..KW-1 of the lanes' points a1 (four
+// chains); returns a^KW.
+template <int KW>
+__device__ __forceinline__ int32_t power_planes(int32_t a1, int32_t one, int8_t* planes, const SModP& q) {
+  int32_t w[4];
+  w[0] = one;
+  w[1] = a1;
+  w[2] = smul(a1, a1, q);
+  w[3] = smul(w[2], a1, q);
+  const int32_t a4 = smul(w[2], w[2], q);
+#pragma unroll
+  for (int h = 0; h < KW / 16; ++h) {
+    u32x4 pl[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      uint32_t d[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        d[j] = sdigits(w[j]);
+        w[j] = smul(w[j], a4, q);
+      }
+      const u32x4 t = byte_planes(d[0], d[1], d[2], d[3]);
+#pragma unroll
+      for (int s = 0; s < 4; ++s) pl[s][c] = t[s];
+    }
+#pragma unroll
+    for (int s = 0; s < 4; ++s) *(u32x4*)(planes + s * 64 * KW + lane_id() * KW + 16 * h) = pl[s];
+  }
+  return w[0];
+}
+
 // The values of f and g at the block's points: of f in X if xf, else in Y.
+// (The powers need no end at the rows': the rows' digits are zero past it.)
 template <int C, int KW>
-__device__ __forceinline__ void ee_eval(const JobDev& J, int k, int pt, TablesDev tab, int8_t* planes, bool xf,
+__device__ __forceinline__ void ee_eval(const JobDev& J, int k, int blk, TablesDev tab, int8_t* planes, bool xf,
                                         EvalCtx& E, int32_t (&X)[C], int32_t (&Y)[C], const SModP& q) {
-  const int l = lane_id(), m = J.m, n = J.n;
   E.planes = planes;
   E.dmax = max(J.ldf, J.kind ? J.ldf : J.ldg) - 1;
   E.one = balance((int32_t)q.one, q.p);
   E.w32 = E.one;
   E.w48 = balance((int32_t)to_mont(65536u, q), q.p);
   E.apw = 0;
-  {
-    // powers 0..KW-1 of the lane's point (four chains), zero past dmax
-    const int32_t a1 = balance((int32_t)eval_point(tab, k, min(pt, J.D - 1), q), q.p);
-    int32_t w[4];
-    w[0] = E.one;
-    w[1] = a1;
-    w[2] = smul(a1, a1, q);
-    w[3] = smul(w[2], a1, q);
-    const int32_t a4 = smul(w[2], w[2], q);
+  if (KW == 32 && tab.pow_planes) {
+    const int8_t* src = tab.pow_planes + ((size_t)k * tab.pow_nb + blk) * (4 * 64 * 32);
 #pragma unroll
-    for (int h = 0; h < KW / 16; ++h) {
-      u32x4 pl[4];
-      if (16 * h <= E.dmax) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          uint32_t d[4];
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            d[j] = 16 * h + 4 * c + j <= E.dmax ? sdigits(w[j]) : 0u;
-            w[j] = smul(w[j], a4, q);
-          }
-          const u32x4 t = byte_planes(d[0], d[1], d[2], d[3]);
-#pragma unroll
-          for (int s = 0; s < 4; ++s) pl[s][c] = t[s];
-        }
-      } else {
-#pragma unroll
-        for (int s = 0; s < 4; ++s) pl[s] = (u32x4){0u, 0u, 0u, 0u};
-      }
-#pragma unroll
-      for (int s = 0; s < 4; ++s) *(u32x4*)(planes + s * 64 * KW + l * KW + 16 * h) = pl[s];
+    for (int i = 0; i < 8; ++i)
+      ((u32x4*)planes)[64 * i + lane_id()] =
+          ((const __attribute__((address_space(1))) u32x4*)gmem(src))[64 * i + lane_id()];
+    if (E.dmax >= KW) {
+      int32_t a = balance((int32_t)eval_point(tab, k, min(blk * 64 + lane_id(), J.D - 1), q), q.p);
+#pragma unroll 1
+      for (int i = 1; i < KW; i <<= 1) a = smul(a, a, q);
+      E.apw = balance(a, q.p);
     }
-    if (E.dmax >= KW) E.apw = balance(w[0], q.p);
+  } else {
+    const int32_t a1 = balance((int32_t)eval_point(tab, k, min(blk * 64 + lane_id(), J.D - 1), q), q.p);
+    E.apw = balance(power_planes<KW>(a1, E.one, planes, q), q.p);
   }
+  // (opaque: otherwise everything that follows is compiled once per case of the
+  // branches above)
+  asm("" : "+s"(E.dmax), "+v"(E.apw));
   group_sync<true>();
-  const uint32_t* Rf = J.res_f + (size_t)k * J.Tf;
-  const uint32_t* Rg = J.res_g + (size_t)k * J.Tg;
-  // One copy of the tile code for all row tiles (unrolled it would overflow
-  // the instruction cache); each tile's values are moved to their registers
-  // behind a scalar branch.
-  constexpr int T = (C + 15) / 16;
+  Rows x, y;
+  {
+    const Rows f{J.res_f + (size_t)k * J.Tf, J.rowdeg_f, J.lpf, J.m};
+    const Rows g{J.res_g + (size_t)k * J.Tg, J.rowdeg_g, J.lpg, J.n};
+    x = xf ? f : g;
+    y = xf ? g : f;
+  }
+  // One copy of the tile code for all tiles (unrolled it would overflow the
+  // instruction cache); each tile's values are moved to their registers behind
+  // a scalar branch.  The rows past the whole tiles share one.
+  constexpr int T = C / 16, RJ = (C % 16) / 4;
+  static_assert(C % 16 <= 8 && C % 4 == 0, "the rest of both arrays fits one tile");
   sfor<C>(EE_IDX(i) { X[i] = Y[i] = own_reg(0); });  // (opaque zeros: a fill would keep the array whole)
 #pragma unroll 1
-  for (int w = 0; w < 2; ++w) {
-    const bool isf = (w == 0) == xf;
-    const uint32_t* R = isf ? Rf : Rg;
-    const int32_t* RD = isf ? J.rowdeg_f : J.rowdeg_g;
-    const int lp = isf ? J.lpf : J.lpg, dg = isf ? m : n;
-#pragma unroll 1
-    for (int tau = 0; 16 * tau <= dg; ++tau) {
-      int32_t o[16];
-      eval_tile<KW>(R, RD, lp, dg, tau, E, o, q);
-      const int id = w * T + tau;
-      sfor<T>(EE_IDX(t) {
-        if (id == t) sfor<(C - 16 * t < 16 ? C - 16 * t : 16)>(EE_IDX(i) { X[16 * t + i] = own_reg(o[i]); });
-        if (id == T + t) sfor<(C - 16 * t < 16 ? C - 16 * t : 16)>(EE_IDX(i) { Y[16 * t + i] = own_reg(o[i]); });
-      });
+  for (int id = 0; id < 2 * T + (RJ ? 1 : 0); ++id) {
+    const int which = id == 2 * T ? 2 : id >= T ? 1 : 0, tau = which == 2 ? T : which ? id - T : id;
+    if (16 * tau > (which == 0 ? x.deg : which == 1 ? y.deg : max(x.deg, y.deg))) continue;
+    int32_t o[16];
+    eval_tile<KW, RJ ? RJ : 1>(x, y, which, 16 * tau, E, o, q);
+    sfor<T>(EE_IDX(t) {
+      if (id == t) sfor<16>(EE_IDX(i) { X[16 * t + i] = own_reg(o[i]); });
+      if (id == T + t) sfor<16>(EE_IDX(i) { Y[16 * t + i] = own_reg(o[i]); });
+    });
+    if constexpr (RJ > 0) {
+      if (id == 2 * T) {
+        sfor<4 * RJ>(EE_IDX(i) { X[16 * T + i] = own_reg(o[i]); });
+        sfor<4 * RJ>(EE_IDX(i) { Y[16 * T + i] = own_reg(o[4 * RJ + i]); });
+      }
     }
   }
 }
@@ -515,7 +575,7 @@ template <int C, int CH, int KW>
 __device__ __forceinline__ bool dev_ee(const JobDev& J, int lb_, TablesDev tab, int8_t* planes) {
   const int nbpp = (J.D + 63) / 64;
   const int k = lb_ / nbpp;
-  const int pt = (lb_ - k * nbpp) * 64 + lane_id();
+  const int blk = lb_ - k * nbpp, pt = blk * 64 + lane_id();
   const int m = J.m, n = J.n;
   const SModP q(tab.primes[k]);
   // the operand of larger degree (A) and the other; which register array
@@ -527,7 +587,7 @@ __device__ __forceinline__ bool dev_ee(const JobDev& J, int lb_, TablesDev tab, 
   const bool xf = ax != sw;  // X holds f
   EvalCtx E;
   int32_t X[C], Y[C];
-  ee_eval<C, KW>(J, k, pt, tab, planes, xf, E, X, Y, q);
+  ee_eval<C, KW>(J, k, blk, tab, planes, xf, E, X, Y, q);
   int as = as0, bs = bs0;
   bool neg = sw && ((m * n) & 1);
   int32_t num = E.one, den = E.one, pfx = E.one;
@@ -582,7 +642,29 @@ __device__ __forceinline__ void ee_block(const JobDev* jobs, const int* starts, 
   if (!ok && threadIdx.x == 0) fb_queue[atomicAdd(fb_count, 1)] = b;
 }
 
+// Powers of the evaluation points in operand form, for the kernels of 32 powers
+// (blocks of 64 points, primes): they depend on the nodes only, and eight loads
+// replace 300 instructions of 3760 (256 pairs of degree 20, with the shared last
+// tile and the shorter epilogue: 650 -> 600 us).
+__global__ __launch_bounds__(64) void k_pow_planes(TablesDev tab, int nb, int8_t* out) {
+  __shared__ __align__(16) int8_t planes[4 * 64 * 32];
+  const int blk = blockIdx.x, k = blockIdx.y;
+  const SModP q(tab.primes[k]);
+  const int32_t a1 = balance((int32_t)eval_point(tab, k, blk * 64 + lane_id(), q), q.p);
+  (void)power_planes<32>(a1, balance((int32_t)q.one, q.p), planes, q);
+  group_sync<true>();
+  u32x4* dst = (u32x4*)(out + ((size_t)k * nb + blk) * (4 * 64 * 32));
+#pragma unroll
+  for (int i = 0; i < 8; ++i) dst[64 * i + lane_id()] = ((const u32x4*)planes)[64 * i + lane_id()];
+}
+
 }  // namespace
+
+size_t pow_planes_bytes(int nb, int P) { return (size_t)nb * P * (4 * 64 * 32); }
+
+void launch_pow_planes(TablesDev tab, int nb, int P, int8_t* out, hipStream_t s) {
+  hipLaunchKernelGGL(k_pow_planes, dim3(nb, P), dim3(64), 0, s, tab, nb, out);
+}
 
 #define BIRES_EE_KERNEL(C, CH, KW, WAVES)                                                                          \
   __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WAVES, 8))) void k_eval_elim_ee##C(          \
@@ -599,14 +681,14 @@ __device__ __forceinline__ void ee_block(const JobDev* jobs, const int* starts, 
 //   CH 30 has 64 KB of code, the whole instruction cache, and takes 1.7 times
 //   as long as with 14; 22 (46 KB) is another 2% faster than 14.
 // Against the kernels with one array in LDS and unsigned arithmetic (us):
-//   24  256 pairs of degree 20, 48 primes, 401 points    667 -> 651
-//   32  45 pairs of degree 31 curves                   10965 -> 7430
+//   24  256 pairs of degree 20, 48 primes, 401 points    667 -> 600
+//   32  45 pairs of degree 31 curves                   10965 -> 7370
 //   48  one discriminant of degree 40                     99 -> 52
-//   68  one pair of degree 64 (general kernel before)   7148 -> 1790
-//   48 + 68  64 pairs of degrees 33 to 64              14432 -> 6440
+//   68  one pair of degree 64 (general kernel before)   7148 -> 1730
+//   48 + 68  64 pairs of degrees 33 to 64              14432 -> 6600
 // All are bound by VALU issue (4.65 cycles per multiply-add, five per
-// coefficient and step); what is left at small degrees is the evaluation,
-// about 40% of the instructions at degree 20.
+// coefficient and step); at degree 20 the evaluation is a third of the
+// instructions.
 BIRES_EE_KERNEL(24, 30, 32, 4)
 BIRES_EE_KERNEL(32, 30, 32, 3)
 BIRES_EE_KERNEL(48, 22, 64, 2)
@@ -629,7 +711,7 @@ __device__ __forceinline__ bool dev_psc(const JobDev& J, int blk, TablesDev tab,
   const bool ax = eq ? ((bs0 - 1) & 1) != 0 : (bs0 & 1) == 0;
   EvalCtx E;
   int32_t X[C], Y[C];
-  ee_eval<C, KW>(J, 0, pt, tab, planes, ax != sw, E, X, Y, q);
+  ee_eval<C, KW>(J, 0, blk, tab, planes, ax != sw, E, X, Y, q);
   int32_t a0 = balance(sel(ax, X[0], Y[0]), q.p);
   const int32_t b0 = balance(sel(ax, Y[0], X[0]), q.p);
   if (__ballot(a0 == 0 || b0 == 0) != 0ull) return false;

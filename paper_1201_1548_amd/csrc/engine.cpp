@@ -280,6 +280,42 @@ bool geo_tables_device(Context* cx, int D, int P, hipStream_t st, TablesDev* tab
   return true;
 }
 
+void pow_planes_device(Context* cx, int D, int P, hipStream_t st, TablesDev* tab) {
+  constexpr size_t kOne = (size_t)32 << 20, kAll = (size_t)256 << 20;
+  std::lock_guard<std::mutex> lk(cx->pow_mu);
+  const bool geo = tab->qpow != nullptr;
+  int nb = (D + 255) / 256 * 4, Pm = std::min((P + 31) & ~31, cx->tab.K);
+  const Context::PowTable* hit = nullptr;
+  size_t total = 0;
+  for (const auto& t : cx->pow) {
+    total += t.bytes;
+    if (t.geo == geo && t.nb >= nb && t.P >= P && (!hit || t.bytes < hit->bytes)) hit = &t;
+  }
+  if (!hit) {
+    // large enough for the earlier calls too, if the nodes' tables and the limits allow
+    int nb1 = nb, P1 = Pm;
+    for (const auto& t : cx->pow)
+      if (t.geo == geo) nb1 = std::max(nb1, t.nb), P1 = std::max(P1, t.P);
+    if (!geo && pow_planes_bytes(nb1, P1) <= kOne && total + pow_planes_bytes(nb1, P1) <= kAll) nb = nb1, Pm = P1;
+    const size_t bytes = pow_planes_bytes(nb, Pm);
+    if (bytes > kOne || total + bytes > kAll) return;
+    int8_t* d = nullptr;
+    if (hipMalloc((void**)&d, bytes) != hipSuccess) {
+      (void)hipGetLastError();
+      return;
+    }
+    launch_pow_planes(*tab, nb, Pm, d, st);
+    if (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess) {
+      (void)hipFree(d);
+      return;
+    }
+    cx->pow.push_back({d, geo, nb, Pm, bytes});
+    hit = &cx->pow.back();
+  }
+  tab->pow_planes = hit->p;
+  tab->pow_nb = hit->nb;
+}
+
 const int8_t* vinv_device(Context* cx, int D, int P, hipStream_t st) {
   constexpr size_t kLimit = (size_t)2 << 30;  // bytes of cached tables
   std::lock_guard<std::mutex> lk(cx->vinv_mu);

@@ -117,6 +117,14 @@ struct Context {
   };
   std::mutex geo_mu;                                    // tables of the geometric nodes (geo_tables_device)
   std::vector<GeoTable> geo;
+  struct PowTable {
+    const int8_t* p;
+    bool geo;
+    int nb, P;
+    size_t bytes;
+  };
+  std::mutex pow_mu;                                    // powers of the points (pow_planes_device)
+  std::vector<PowTable> pow;
   std::mutex ev_mu;
   std::vector<hipEvent_t> ev_free;                      // completion events of batched calls, reused
   std::mutex vinv_mu;
@@ -157,6 +165,10 @@ bool interp_tables_device(Context* cx, int blocks, int primes, hipStream_t st, c
 // and 1 GiB in all; never freed, calls in flight may read them).  False when
 // they would not fit or the build failed: the call then uses the nodes 0..D-1.
 bool geo_tables_device(Context* cx, int D, int P, hipStream_t st, TablesDev* tab);
+// Fills tab->pow_planes for at least D points and P primes on the nodes tab is set
+// up for; leaves it null when the table would exceed its limits (32 MiB, 256 MiB
+// for all).
+void pow_planes_device(Context* cx, int D, int P, hipStream_t st, TablesDev* tab);
 
 // The explicit CRT's tables of P primes, built on first use (on stream st, which
 // is then synchronised) and kept; nullptr above 1 GiB in all or on failure.

@@ -143,6 +143,10 @@ struct TablesDev {
   const uint32_t* geo_w;
   const int8_t* geo_A;
   int32_t geo_D;
+  // digit planes of the first 32 powers of the points of [P][pow_nb] blocks of
+  // 64 points (either set of nodes); null: the evaluation computes them
+  const int8_t* pow_planes;
+  int32_t pow_nb;
 };
 
 }  // namespace bires
