@@ -61,6 +61,7 @@ struct Work {
   size_t o_in[2] = {0, 0}, o_scan[2] = {0, 0};
   size_t o_res_f = 0, o_res_g = 0, o_vals = 0, o_coefs = 0, o_digits = 0, o_neg = 0, o_acc_lo = 0, o_acc_hi = 0;
   size_t o_out = 0, o_hout = 0, o_rowdeg = 0;
+  int ucap = 0, ulimbs = 1;  // the output's capacities; degcap, Lout: of the device's copy
 };
 
 // Holder of one pool block (given back when the holder goes).
@@ -443,8 +444,14 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
         x.status = BIRES_EBUFSIZE;
         continue;
       }
-      x.degcap = o->degree;
-      x.Lout = o->limbs;
+      x.degcap = x.ucap = o->degree;
+      x.Lout = x.ulimbs = o->limbs;
+      // a result in host memory crosses the bus with the rows and limbs that the
+      // plan bounds (bounds from the shapes alone are a few times that)
+      if (mem == BIRES_MEM_HOST && !noalloc && x.pl.kind_special == 0) {
+        x.degcap = x.pl.D - 1;
+        x.Lout = need_limbs;
+      }
     }
     x.active = x.pl.kind_special == 0;
     if (x.active) {
@@ -512,8 +519,8 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
       x.o_acc_lo = ws.take((size_t)p.D * x.Lacc * 8);
       x.o_acc_hi = ws.take((size_t)p.D * x.Lacc * 4);
       if (mem == BIRES_MEM_HOST) {
-        x.o_out = ws.take((size_t)(x.degcap + 1) * x.Lout * 4);
         x.o_hout = hout.take((size_t)(x.degcap + 1) * x.Lout * 4);
+        if (noalloc) x.o_out = ws.take((size_t)(x.degcap + 1) * x.Lout * 4);
       }
     }
     maxP = std::max(maxP, p.P);
@@ -696,6 +703,10 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
   const size_t o_ffbq = ws.take(sizeof(int) * (fused ? (size_t)fst_rg[nj] : 0));
   size_t o_fbq[NRG];  // queues of blocks recomputed by the LDS kernel
   for (int r = 0; r < NRG; ++r) o_fbq[r] = ws.take(sizeof(int) * (size_t)starts[K_RG0 + r][nj]);
+  // results for host memory: one region, one copy back
+  const size_t o_outs = ws.take(noalloc ? 0 : hout.bytes);
+  if (!noalloc)
+    for (Work& x : w) x.o_out = o_outs + x.o_hout;
   // metadata uploaded with one copy: descriptors, flags, row degrees, block maps
   const size_t meta_begin = ws.take(0);
   const size_t o_jobs = ws.take(sizeof(JobDev) * (size_t)nj);
@@ -1026,7 +1037,11 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
     sg.add(nj, o_flags, (const void*)h_flags);
     if (run && nj)
       DEV(hipMemcpyAsync(h_flags, D0 + o_flags, sizeof(int32_t) * (2 * nj + 3), hipMemcpyDeviceToHost, st));
-    for (int i = 0; i < nj; ++i) {
+    if (!noalloc) {
+      sg.add((const void*)hob, o_outs, hout.bytes);
+      if (run && hout.bytes) DEV(hipMemcpyAsync(hob, D0 + o_outs, hout.bytes, hipMemcpyDeviceToHost, st));
+    }
+    for (int i = 0; i < nj && noalloc; ++i) {
       const Work& x = w[i];
       if (x.status || !x.active || mem != BIRES_MEM_HOST) continue;
       sg.add(i, (const void*)hob, x.o_hout, x.o_out, x.degcap, x.Lout);
@@ -1098,6 +1113,29 @@ void set_pending_stream_lock(PendingBatch* pending) {
   if (pending) pending->lock_stream = true;
 }
 
+namespace {
+
+// A result of (degcap + 1) rows of Lout limbs into its buffer of (ucap + 1) rows
+// of ulimbs: clear_result, while the device works, then fill_result.
+void clear_result(const Work& x, uint32_t* dst) {
+  const size_t done = x.ulimbs == x.Lout ? (size_t)(x.degcap + 1) * x.ulimbs : 0;
+  std::memset(dst + done, 0, ((size_t)(x.ucap + 1) * x.ulimbs - done) * 4);
+}
+
+void fill_result(const Work& x, const uint32_t* src, uint32_t* dst) {
+  const size_t L = x.Lout, U = x.ulimbs;
+  if (U == L) {
+    std::memcpy(dst, src, (size_t)(x.degcap + 1) * L * 4);
+    return;
+  }
+  for (int r = 0; r <= x.degcap; ++r, src += L, dst += U) {
+    std::memcpy(dst, src, L * 4);
+    if (src[L - 1] >> 31) std::memset(dst + L, 0xff, (U - L) * 4);
+  }
+}
+
+}  // namespace
+
 int run_batch_finish(PendingPtr P) {
   if (!P) return BIRES_EINVAL;
   Context* cx = P->cx;
@@ -1110,6 +1148,9 @@ int run_batch_finish(PendingPtr P) {
   const size_t scan_words = P->scan_words;
   SpecCache& sc = cx->spec;
   hc.resume();
+  if (mem == BIRES_MEM_HOST)
+    for (int i = 0; i < nj; ++i)
+      if (!w[i].status && w[i].active) clear_result(w[i], jobs[i].out->c);
   if (P->noalloc)
     DEV(hipStreamSynchronize(P->st));
   else
@@ -1201,7 +1242,7 @@ int run_batch_finish(PendingPtr P) {
           x.status = BIRES_ECHECK;
         } else {
           if (mem == BIRES_MEM_HOST)
-            std::memcpy(o->c, P->hout_base + x.o_hout, (size_t)(x.degcap + 1) * x.Lout * 4);
+            fill_result(x, (const uint32_t*)(P->hout_base + x.o_hout), o->c);
           o->degree = h_flags[2 * i];
         }
       } else {
