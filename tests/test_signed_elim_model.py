@@ -82,6 +82,37 @@ def test_remainder_chain_keeps_the_bound(prime):
     assert abs(balance(one, p)) <= p // 2
 
 
+def test_paired_division_steps_keep_their_bound(prime):
+    # A[j] <- A[j+2] + y1 B[j+2] + y0 B[j+1] with 1 / lc(B) balanced: |A| <= 1.3 p throughout
+    p = prime
+    rng = random.Random(p + 2)
+    one, ri = balance(W % p, p), pow(W, -1, p)
+    for ext in (False, True):
+        pick = (lambda: rng.choice([9 * p // 8, -(9 * p // 8)])) if ext else (lambda: rng.randint(-p, p))
+        m, n = 31, 6
+        A, B = [pick() for _ in range(m + 1)], [pick() for _ in range(n + 1)]
+        lb = balance(B[0], p)
+        ninv = redc(-pow(lb, -1, p) * pow(W, 2, p) % p * W, p)  # any representative up to 0.6 p
+        ninv = balance(ninv, p) if abs(ninv) > 0.6 * p else ninv
+        ref = [a % p for a in A]
+        Bp = B + [0] * (m + 3)
+        ap = m
+        while ap > n:
+            y1 = redc(A[0] * ninv, p)
+            y0 = redc(redc(one * A[1] + y1 * Bp[1], p) * ninv, p)
+            assert max(abs(y1), abs(y0)) <= 0.76 * p
+            A = A + [0, 0]
+            A = [redc(one * A[j + 2] + y1 * Bp[j + 2] + y0 * Bp[j + 1], p) if j < n else A[j + 2]
+                 for j in range(len(A) - 2)][: ap - 1]
+            assert max(abs(a) for a in A) <= 1.3 * p
+            for _ in range(2):
+                q = ref[0] * pow(B[0], -1, p) % p
+                ref = [(ref[j + 1] - q * Bp[j + 1]) % p for j in range(len(ref) - 1)]
+            assert [a % p for a in A] == ref
+            ap -= 2
+    assert ri * W % p == 1
+
+
 @pytest.mark.parametrize("kw", [32, 64])
 def test_digit_products_join_in_the_given_widths(prime, kw):
     p = prime
