@@ -50,23 +50,18 @@ __device__ __forceinline__ uint32_t lane_up(uint32_t x) {
 }
 __device__ __forceinline__ uint32_t lane_of(uint32_t x, int l) { return __builtin_amdgcn_readlane(x, l); }
 
-// One normal step (A of degree deg B + 1) on top-aligned lanes:
-// R = l2 A + (l1 y + n2) B with the constants of eliminate().
-struct StepConst {
-  uint32_t l2, l1, n2;
-};
-__device__ __forceinline__ StepConst step_const(uint32_t A, uint32_t B, const ModP& q) {
-  const uint32_t lb = lane_of(B, 0), b1 = lane_of(B, 1), a0 = lane_of(A, 0), a1 = lane_of(A, 1);
-  const uint32_t n1 = mneg_factor(a0, q.p);
-  StepConst c;
-  c.n2 = mneg_factor(mdot2(lb, a1, n1, b1, q), q.p);
-  c.l2 = mmul(lb, lb, q);
-  c.l1 = mmul(lb, n1, q);
-  return c;
-}
-__device__ __forceinline__ uint32_t step_rem(uint32_t A, uint32_t B, const StepConst& c, const ModP& q) {
-  const uint32_t B1 = lane_down(B), B2 = lane_down(B1), A2 = lane_down(lane_down(A));
-  return mdot3(c.l2, A2, c.l1, B2, c.n2, B1, q);
+// One normal step (A of degree deg B + 1) on top-aligned lanes as two
+// eliminations: T = lb A - a0 y B, R = lb T - t0 B, with lb and an0 = p - a0 the scalar
+// multipliers, and tn0 = p - t0 for the caller.  (Its three-product form R = l2 A +
+// (l1 y + n2) B has a shorter chain in the lanes, but computes its three
+// constants in scalar registers: 36 more instructions on a wave that waits for
+// each of them.)
+__device__ __forceinline__ uint32_t step_rem(uint32_t A, uint32_t B, uint32_t lb, uint32_t an0, uint32_t& tn0,
+                                             const ModP& q) {
+  const uint32_t B1 = lane_down(B);
+  const uint32_t T = mdot2(lb, lane_down(A), an0, B1, q);
+  tn0 = mneg_factor(lane_of(T, 0), q.p);
+  return mdot2(lb, lane_down(T), tn0, B1, q);
 }
 
 // Up to 31 normal steps of a wave on the top 64 coefficients A, B (lane i: the
@@ -85,12 +80,15 @@ __device__ __forceinline__ int window_steps(const uint32_t A0, const uint32_t B0
     // no harm here: the steps run without a branch, and if there was one the
     // steps before it are run again
     int zero = TAPS;
+    uint32_t an0 = mneg_factor(lane_of(A, 0), q.p), lb = lane_of(B, 0);
 #pragma unroll 2
     for (int i = 0; i < s; ++i) {
-      const StepConst c = step_const(A, B, q);
-      const uint32_t R = step_rem(A, B, c, q);
-      const uint32_t MR = mdot3(c.l2, MA, c.l1, lane_up(MB), c.n2, MB, q);
-      if (lane_of(R, 0) == 0u) zero = min(zero, i);
+      uint32_t tn0;
+      const uint32_t R = step_rem(A, B, lb, an0, tn0, q);
+      const uint32_t MR = mdot2(lb, mdot2(lb, MA, an0, lane_up(MB), q), tn0, MB, q);
+      an0 = mneg_factor(lb, q.p);
+      lb = lane_of(R, 0);
+      if (lb == 0u) zero = min(zero, i);
       A = B;
       B = R;
       MA = MB;
@@ -307,7 +305,8 @@ __device__ int block_gcd_fp(uint32_t*& X, uint32_t*& Y, uint32_t*& X2, uint32_t*
         uint32_t A = l <= a ? X[a - l] : 0u, B = l <= b ? Y[b - l] : 0u;
         int bb = b;
         while (bb >= 1) {
-          const uint32_t R = step_rem(A, B, step_const(A, B, q), q);
+          uint32_t tn0;
+          const uint32_t R = step_rem(A, B, lane_of(B, 0), mneg_factor(lane_of(A, 0), q.p), tn0, q);
           if (lane_of(R, 0) == 0u) break;
           A = B;
           B = R;
