@@ -273,6 +273,7 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
   Layout in;
   std::vector<ScanTask> tasks;
   std::vector<int4> smap;
+  int swaves = 1;
   for (int i = 0; i < nj; ++i) {
     if (w[i].status) continue;
     for (int which = 0; which < nsrc(i); ++which) {
@@ -293,6 +294,7 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
         in.bytes += (size_t)s.rows * ROWSTAT_WORDS * 4;
         for (int r0 = 0; r0 < s.rows; r0 += 64) smap.push_back(make_int4((int)tasks.size(), r0, 0, 0));
         tasks.push_back(ScanTask{});
+        swaves = std::max(swaves, scan_waves(s.rows, s.ld, s.L));
       }
     }
   }
@@ -386,7 +388,7 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
                          hipMemcpyHostToDevice, st));
     hc.mark(0);
     if (!smap.empty())
-      launch_scan((const ScanTask*)(hmap + o_tasks), (const int4*)(hmap + o_smap), (int)smap.size(), st);
+      launch_scan((const ScanTask*)(hmap + o_tasks), (const int4*)(hmap + o_smap), (int)smap.size(), swaves, st);
     hc.mark(1);
     if (!spec) {
       if (noalloc && scan_words)

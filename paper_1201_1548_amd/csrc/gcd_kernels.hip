@@ -18,9 +18,9 @@
 // 512 threads: seven waves apply a matrix in less time than the one wave takes
 // for its 31 steps (about 70 instructions each, one dependent chain), which
 // is what a round now waits for; that wave runs at a raised priority.
-// Measured for a degree-1560 pair: k_gcd_p, 115 primes, 1393 -> 323 us; with a
-// common factor of degree 200 and the two exact divisions 1090 -> 307 us;
-// k_fiber_chain (two chains, one block each) 2525 -> 327 us.
+// Measured for a degree-1560 pair: k_gcd_p, 115 primes, 1393 -> 265 us; with a
+// common factor of degree 200 and the two exact divisions 1090 -> 280 us;
+// k_fiber_chain (two chains, one block each) 2525 -> 259 us.
 #include <hip/hip_runtime.h>
 
 #include "device.hpp"

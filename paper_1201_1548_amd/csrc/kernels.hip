@@ -43,23 +43,29 @@ namespace bires {
 // (double, raised by 2^-52), the sum by ld 2^-53 relative rounding (raised by
 // 2^-40), the logarithm by 10^-6.
 
-__device__ __forceinline__ double mag_upper(const uint32_t* c, int L) {
-  const uint32_t inv = (c[L - 1] >> 31) ? 0xFFFFFFFFu : 0u;  // |c| <= (c xor sign) + 1
-  int t = L - 1;
-  while (t > 0 && (c[t] ^ inv) == 0u) --t;
-  const uint64_t top = t ? (((uint64_t)(c[t] ^ inv) << 32) | (c[t - 1] ^ inv)) : (uint64_t)(c[0] ^ inv);
-  const double v = ((double)top + 1.0) * (1.0 + 0x1p-52);
-  return t ? ldexp(v, 32 * (t - 1)) : v;
+// Lanes of a row of ld coefficients: a power of two from 4 to 64 (longer rows in
+// pieces of 64).
+__host__ __device__ __forceinline__ int scan_row_lanes(int ld) {
+  int w = 4;
+  while (w < 64 && w < ld) w <<= 1;
+  return w;
 }
 
+// A block's 64 rows are dealt to its waves, 64 / w rows of w lanes at a time.
+// The 1-norm is added up in the order of the coefficients (one lane's value
+// after the other), so that it does not depend on w.  With one lane per row a pair
+// of degree 64 with coefficients of 4 limbs took 73 us (65 x 65 dependent loads),
+// 35 this way; 1000 pairs of degree 6 24 and 18.  Longer rows of one limb keep one
+// lane, which reads eight words at a time (256 pairs of degree 20: 11 us, 14 with
+// 32 lanes).
 __global__ void k_scan(const ScanTask* tasks, const int4* bmap) {
-  int4 bm = bmap[blockIdx.x];
-  const ScanTask& T = tasks[bm.x];
-  int j = bm.y + threadIdx.x;
-  if (j >= T.rows) return;
-  int deg = -1, bits = 0, cnt = 0;
-  double norm = 0.0;
-  if (T.L == 1) {
+  const int4 bm = bmap[blockIdx.x];
+  const ScanTask T = tasks[bm.x];
+  if (T.L == 1 && T.ld > 8) {
+    const int j = bm.y + (int)threadIdx.x;
+    if (threadIdx.x >= 64 || j >= T.rows) return;
+    int deg = -1, bits = 0, cnt = 0;
+    double norm = 0.0;
     // one-limb coefficients: the row's words eight at a time (loads first),
     // each handled as below, in the same order
     const uint32_t* rowp = T.limbs + (size_t)j * T.ld;
@@ -85,30 +91,57 @@ __global__ void k_scan(const ScanTask* tasks, const int4* bmap) {
     T.out[4 * j + 3] = cnt ? (int32_t)ceil((log2(norm * (1.0 + 0x1p-40)) + 1e-6) * 1024.0) : 0;
     return;
   }
-  for (int i = 0; i < T.ld; ++i) {
-    const uint32_t* c = T.limbs + ((size_t)j * T.ld + i) * T.L;
-    uint32_t top = c[T.L - 1];
-    uint32_t inv = (top >> 31) ? 0xFFFFFFFFu : 0u;   // |c| <= (c xor sign) + 1
-    int b = 0;
-    bool nz = false;
-    for (int l = T.L - 1; l >= 0; --l) {
-      uint32_t w = c[l];
-      nz |= (w != 0u);
-      uint32_t x = w ^ inv;
-      if (b == 0 && x != 0u) b = 32 * l + (32 - __clz(x));
+  const int w = scan_row_lanes(T.ld), R = 64 / w;
+  const int l = lane_id(), li = l & (w - 1), base = l & ~(w - 1);
+  const int r1 = min(T.rows, bm.y + 64), nw = (int)blockDim.x >> 6;
+  for (int r = bm.y + (int)(threadIdx.x >> 6) * R; r < r1; r += nw * R) {
+    const int j = r + l / w;
+    const bool act = j < r1;
+    int deg = -1, bits = 0, cnt = 0;
+    double norm = 0.0;
+    for (int i0 = 0; i0 < T.ld; i0 += w) {
+      double v = 0.0;
+      bool nz = false;
+      if (act && i0 + li < T.ld) {
+        const uint32_t* c = T.limbs + ((size_t)j * T.ld + i0 + li) * T.L;
+        // |c| <= (c xor sign) + 1; t: highest limb of that (0 if none), hi and
+        // lo: limbs t and t - 1
+        const uint32_t inv = (c[T.L - 1] >> 31) ? 0xFFFFFFFFu : 0u;
+        int t = 0;
+        uint32_t hi = 0u, lo = 0u;
+        for (int q = T.L - 1; q >= 0; --q) {
+          const uint32_t x = c[q] ^ inv;
+          if (hi == 0u) {
+            hi = x;
+            t = q;
+          } else if (q == t - 1) {
+            lo = x;
+          }
+        }
+        nz = hi != 0u || inv != 0u;
+        if (nz) {
+          bits = max(bits, 32 * t + (hi ? 32 - __clz(hi) : 0) + (inv ? 1 : 0));
+          const uint64_t top = t ? ((uint64_t)hi << 32) | lo : (uint64_t)hi;
+          v = ((double)top + 1.0) * (1.0 + 0x1p-52);
+          if (t) v = ldexp(v, 32 * (t - 1));
+        }
+      }
+      const uint64_t m = (__ballot(nz) >> base) & (w == 64 ? ~0ull : (1ull << w) - 1ull);
+      if (m) deg = i0 + 63 - __clzll((long long)m);
+      cnt += __popcll(m);
+      const int n = min(w, T.ld - i0);
+      for (int u = 0; u < n; u += 4) {  // (zeros past n)
+        double x[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) x[k] = __shfl(v, base + u + k);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) norm += x[k];
+      }
     }
-    if (nz) {
-      deg = i;
-      ++cnt;
-      b += inv ? 1 : 0;
-      bits = b > bits ? b : bits;
-      norm += mag_upper(c, T.L);
-    }
+    for (int d = 1; d < w; d <<= 1) bits = max(bits, __shfl_xor(bits, d));
+    const int fx = cnt ? (int32_t)ceil((log2(norm * (1.0 + 0x1p-40)) + 1e-6) * 1024.0) : 0;
+    if (act && li < 4) T.out[4 * j + li] = li == 0 ? deg : li == 1 ? bits : li == 2 ? cnt : fx;
   }
-  T.out[4 * j + 0] = deg;
-  T.out[4 * j + 1] = bits;
-  T.out[4 * j + 2] = cnt;
-  T.out[4 * j + 3] = cnt ? (int32_t)ceil((log2(norm * (1.0 + 0x1p-40)) + 1e-6) * 1024.0) : 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -2621,8 +2654,14 @@ void launch_stats_check(const int32_t* got, const int32_t* want, long long n, in
   if (blocks > 0) hipLaunchKernelGGL(k_stats_check, dim3((unsigned)blocks), dim3(256), 0, s, got, want, n, flag);
 }
 
-void launch_scan(const ScanTask* tasks, const int4* bmap, int nblocks, hipStream_t s) {
-  hipLaunchKernelGGL(k_scan, dim3(nblocks), dim3(64), 0, s, tasks, bmap);
+int scan_waves(int rows, int ld, int L) {
+  return L == 1 && ld > 8 ? 1 : (std::min(rows, 64) * scan_row_lanes(ld) + 63) / 64;
+}
+
+void launch_scan(const ScanTask* tasks, const int4* bmap, int nblocks, int waves, hipStream_t s) {
+  // as many waves as the largest rectangle has use for, up to 32 per SIMD in all
+  const int nw = std::max(1, std::min({waves, 16, 32768 / nblocks}));
+  hipLaunchKernelGGL(k_scan, dim3(nblocks), dim3(64 * nw), 0, s, tasks, bmap);
 }
 
 void launch_transpose(const uint32_t* src, uint32_t* dst, int rows, int cols, int L, hipStream_t s) {

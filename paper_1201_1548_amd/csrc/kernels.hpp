@@ -15,7 +15,9 @@ struct ScanTask {
   int32_t* out;
 };
 
-void launch_scan(const ScanTask* tasks, const int4* bmap, int nblocks, hipStream_t s);
+// waves: the largest scan_waves of the tasks
+int scan_waves(int rows, int ld, int L);
+void launch_scan(const ScanTask* tasks, const int4* bmap, int nblocks, int waves, hipStream_t s);
 // Issue-rate probe: kind 0..5 = v_add_u32, v_min_u32, v_mul_lo_u32,
 // v_mad_u64_u32, v_fma_f64 (16 chains per lane), v_mfma_i32_32x32x32_i8
 // (16 products per round over 4 accumulators); `iters` rounds; out holds
