@@ -114,9 +114,9 @@ void launch_crt_tables(TablesDev tab, int P, int LM, uint32_t* buf, hipStream_t 
 // the chip idle at a few thousand rows.  Bound: the right operand's traffic
 // from L2, 16 P LM bytes per block.  Measured against Garner's digits, limb sums
 // and carries (a wave's chain of P^2 / 2 products per coefficient): 573 primes
-// and 4097 coefficients (one degree-64 resultant) 2290 -> 252 us; 64 serving
-// requests 4550 -> 640 us with the small counts' launches; the three
-// polynomials of a degree-1560 gcd over 150 primes 308 -> 57 us.
+// and 4097 coefficients (one degree-64 resultant) 2290 -> 143 us; 64 serving
+// requests 4550 -> 520 us with the small counts' launches; the three
+// polynomials of a degree-1560 gcd over 150 primes 308 -> 55 us.
 namespace {
 constexpr int CBW = 8;          // waves per block
 constexpr int CB_TAIL = 20;     // limbs at and above the output's limb count kept for the range check
@@ -207,11 +207,17 @@ __global__ __launch_bounds__(64 * CBW) void k_crt_big(const JobDev* jobs, const 
     const int64_t t = tq[row];
     const bool live = c0 + row <= J.degcap;
     uint32_t* orow = J.out + (size_t)(c0 + row) * Lc;
+    // Every wave starts its chains at another step: in step with each other the
+    // waves of all blocks would ask the same few channels of the L2 for the same
+    // lines (a step is 1 KiB, the channels repeat every 4 KiB): 252 us instead of 143
+    // for 573 primes and 4097 coefficients.
+    const int k0 = (int)((unsigned)(wv * 9 + bj * 5) % (unsigned)KS);
     for (int ct = wv; ct < NCT; ct += CBW) {
       im_v16i acc = {0};
       const __attribute__((address_space(1))) uint32_t* Bc = Bt + (size_t)ct * KS * 256;
 #pragma unroll 8
-      for (int ks = 0; ks < KS; ++ks) {
+      for (int i = 0; i < KS; ++i) {
+        const int ks = i + k0 < KS ? i + k0 : i + k0 - KS;
         const im_v4i a = *(const im_v4i*)(A + ks * 256 + 4 * l);
         const im_v4i b = *(const __attribute__((address_space(1))) im_v4i*)(Bc + (size_t)ks * 256);
         acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, acc, 0, 0, 0);
