@@ -32,9 +32,9 @@
 //
 // Measured against the per-(job, prime) kernel on the nodes 0..D-1 (a VALU
 // convolution and a Horner recurrence over D / 32 blocks with a barrier each):
-// one degree-40 discriminant (D = 1561, 55 primes) 194 -> 24 us, one degree-64
-// resultant (D = 4097, 573 primes) 2604 -> 305 us, 3800 arrangement pairs
-// (D 17..901) 5026 -> 1283 us, 64 serving requests (D up to 4097) 5085 -> 780 us.
+// one degree-40 discriminant (D = 1561, 55 primes) 194 -> 22 us, one degree-64
+// resultant (D = 4097, 573 primes) 2604 -> 187 us, 3800 arrangement pairs
+// (D 17..901) 5026 -> 895 us, 64 serving requests (D up to 4097) 5085 -> 500 us.
 #include <hip/hip_runtime.h>
 
 #include "device.hpp"
@@ -167,8 +167,16 @@ __device__ __forceinline__ uint32_t geo_value(const im_v4i (&G)[7], int j, const
 // One block of TW waves per (job, prime).  LDS: two sets of four digit planes
 // of PS = 256 (nt + 1) bytes (256 zero bytes, then nt = ceil(D / 256) tiles).
 // PAIR: a wave takes the tile pair (nt - 1 - pr, pr); without it one tile.
+// The left operand of the next window, with several waves of the next two, is on its
+// way (a window lasts 272 or 544 cycles, a miss in the L2, which does not hold the
+// tables of all primes at work, longer).  Two waves per SIMD at least: with the
+// default of one the compiler keeps the sums in accumulation registers and
+// copies them out and back in every window (84 copies to 32 products: 301 instead
+// of 187 us for D = 4097 and 573 primes).
 template <int TW, bool PAIR>
-__global__ __launch_bounds__(64 * TW) void k_interp_geo(const JobDev* jobs, const int* starts, int nj, TablesDev tab) {
+__global__ __launch_bounds__(64 * TW) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_interp_geo(
+    const JobDev* jobs, const int* starts, int nj, TablesDev tab) {
+  constexpr int AHEAD = TW == 1 ? 1 : 2;
   extern __shared__ __align__(16) int8_t geo_lds[];
   const int job = find_job(starts, nj, blockIdx.x, gridDim.x);
   const JobDev& J = jobs[job];
@@ -243,29 +251,37 @@ __global__ __launch_bounds__(64 * TW) void k_interp_geo(const JobDev* jobs, cons
       im_v4i Gh[7], Gl[PAIR ? 7 : 1];
 #pragma unroll
       for (int u = 0; u < 7; ++u) Gh[u] = (im_v4i){0, 0, 0, 0};
-      im_v4i a[4], an[4], b[4];
-      geo_load_a(a, At, 0);
+      im_v4i a[AHEAD + 1][4], b[4];
+#pragma unroll
+      for (int i = 0; i < AHEAD; ++i) geo_load_a(a[i], At, min(i, Wh - 1));
+      auto next = [&](int w) {
+        geo_load_a(a[AHEAD], At, min(w + AHEAD, Wh - 1));
+      };
+      auto shift = [&] {
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i)
+#pragma unroll
+          for (int s = 0; s < 4; ++s) a[i][s] = a[i + 1][s];
+      };
       int w = 0;
       if constexpr (PAIR) {
 #pragma unroll
         for (int u = 0; u < 7; ++u) Gl[u] = (im_v4i){0, 0, 0, 0};
         for (; w < Wl; ++w) {
-          geo_load_a(an, At, min(w + 1, Wh - 1));
+          next(w);
           im_v4i c[4];
           geo_load_b(b, xh - 64 * w, PS);
           geo_load_b(c, xl - 64 * w, PS);
-          geo_products(Gh, a, b);
-          geo_products(Gl, a, c);
-#pragma unroll
-          for (int s = 0; s < 4; ++s) a[s] = an[s];
+          geo_products(Gh, a[0], b);
+          geo_products(Gl, a[0], c);
+          shift();
         }
       }
       for (; w < Wh; ++w) {
-        geo_load_a(an, At, min(w + 1, Wh - 1));
+        next(w);
         geo_load_b(b, xh - 64 * w, PS);
-        geo_products(Gh, a, b);
-#pragma unroll
-        for (int s = 0; s < 4; ++s) a[s] = an[s];
+        geo_products(Gh, a[0], b);
+        shift();
       }
       finish(Gh, hi);
       if constexpr (PAIR) {
