@@ -34,7 +34,7 @@ def int_peak_tops(dev):
     return dev["cus"] * LANES_PER_CU_CLOCK * dev["clock_khz"] * 1e3 / 1e12
 
 
-TRAFFIC_SOURCES = ("kernels.hip", "kernels.hpp", "job.hpp", "modp.hpp")
+TRAFFIC_SOURCES = ("ee.hip", "kernels.hip", "kernels.hpp", "device.hpp", "job.hpp", "modp.hpp")
 
 
 def kernel_source_digest():
@@ -637,7 +637,7 @@ def main():
     instances = P * D * n
     avg_ms = kms / max(launches, 1)
     peak = int_peak_tops(dev)
-    per_inst = stored_counters("valu", "k_eval_elim_rg24", workload, "int_lane_ops_per_instance")
+    per_inst = stored_counters("valu", "k_eval_elim_ee24", workload, "int_lane_ops_per_instance")
     achieved = None if per_inst is None else per_inst * instances / (avg_ms / 1e3) / 1e12
     rowdeg = [20 - j for j in range(21)]
     mulmods = model_mulmods(rowdeg, rowdeg)
@@ -647,13 +647,13 @@ def main():
         "peak": round(peak, 2),
         "unit": "T int32-lane-op/s",
         "frac": None if achieved is None else round(achieved / peak, 4),
-        "traffic": stored_traffic("k_eval_elim_rg24", workload),
+        "traffic": stored_traffic("k_eval_elim_ee24", workload),
         "traffic_unit": "bytes per launch",
-        "kernel": "k_eval_elim_rg24 (+ k_eval_elim_fb)",
+        "kernel": "k_eval_elim_ee24 (+ k_eval_elim_fb)",
         "kernel_ms": round(avg_ms, 4),
         "instances_per_launch": instances,
         "int_lane_ops_per_instance": per_inst,
-        "counters": "profiles/valu_k_eval_elim_rg24_%s.md" % workload,
+        "counters": "profiles/valu_k_eval_elim_ee24_%s.md" % workload,
         "model_mulmods_per_instance": mulmods,
         "model_mulmod_rate_T_per_s": round(mulmods * instances / (avg_ms / 1e3) / 1e12, 3),
     }

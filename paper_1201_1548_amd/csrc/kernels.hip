@@ -2095,10 +2095,12 @@ __device__ __forceinline__ void dev_crt(const JobDev* jobs, const int* starts, i
 // The staged kernel keeps its own copy of the body above (with two operand
 // sets up to 64 primes): called through the device function, the compiler
 // schedules the operand loads differently and takes 255 VGPRs for 48 primes
-// (one wave per SIMD, 30 -> 44 us for 256 degree-20 pairs) instead of 150.
+// (one wave per SIMD, 30 -> 44 us for 256 degree-20 pairs) instead of 150.  For 97
+// to 128 primes two waves per SIMD are asked for (256 registers otherwise: 85 us
+// instead of 55 for the arrangement's).
 template <int KSMAX, int NT>
-__global__ __launch_bounds__(64) void k_crt_mfma(const JobDev* jobs, const int* starts, int nj, int sld, int cps,
-                                                 TablesDev tab) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(KSMAX == 16 ? 2 : 1, 8))) void k_crt_mfma(
+    const JobDev* jobs, const int* starts, int nj, int sld, int cps, TablesDev tab) {
   constexpr int ROWS = 32 * NT;
   extern __shared__ __align__(16) uint32_t lds[];
   const int l = threadIdx.x, x = l & 31, g = l >> 5;
