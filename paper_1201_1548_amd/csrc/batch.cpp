@@ -7,6 +7,7 @@
 
 #include "engine.hpp"
 #include "kernels.hpp"
+#include "scratch.hpp"
 #include "tables.hpp"
 
 namespace bires {
@@ -733,7 +734,8 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
   if (noalloc) {
     // the workspace follows the input region in the scratch array
     const size_t base = (in.bytes + 255) & ~(size_t)255;
-    if (base + ws.bytes > cx->scratch_bytes) return BIRES_ETOOBIG;
+    const size_t beside = sizeof(int) * (size_t)starts[K_RG0 + NRG - 1][nj] + 1024;
+    if (base + ws.bytes > cx->scratch_bytes + std::min(beside, NOALLOC_MARGIN)) return BIRES_ETOOBIG;
     D0 = cx->scratch + base;
     P->hv_meta.resize(meta_end - meta_begin);
     P->hv_out.resize(hout.bytes);

@@ -7,10 +7,11 @@
 #include <stdint.h>
 
 #include "../../include/bires.h"
+#include "scratch.hpp"
 
 namespace bires {
 
-static __device__ __align__(256) uint8_t scratch[BIRES_NOALLOC_SCRATCH_BYTES];
+static __device__ __align__(256) uint8_t scratch[BIRES_NOALLOC_SCRATCH_BYTES + NOALLOC_MARGIN];
 
 // Called once per device at library set-up, with that device current.
 int scratch_address(uint8_t** ptr, size_t* bytes) {
