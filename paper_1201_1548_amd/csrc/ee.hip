@@ -160,8 +160,17 @@ struct Rows {
 // slot rho of the matrix tile holds row 4 (rho % 4) + rho / 4, so that register j
 // of lane group g is row 4 j + g: the slots past the degree are whole registers
 // and their epilogue is skipped.
+//
+// Pieces of KW coefficients: piece `part` alone, which returns false (and no
+// values) if no row of the tile reaches it, or (part < 0) all of them, joined by
+// Horner's rule in a^KW.
+//
+// Rows shorter than the tile's pieces are read past their end and masked: at most
+// the longest row's coefficients and 64 more from the start of the last row on, which
+// the point count (at least one more than any x-degree) keeps inside the values
+// that follow the residues and their slack.
 template <int KW, int RJ>
-__device__ __forceinline__ void eval_tile(const Rows& x, const Rows& y, int which, int base, const EvalCtx& E,
+__device__ __forceinline__ bool eval_tile(const Rows& x, const Rows& y, int which, int base, int part, const EvalCtx& E,
                                           int32_t (&out)[16], const SModP& q0) {
   typedef Oper<KW> OP;
   constexpr int NQ = KW / 16;  // quads of coefficients per lane
@@ -188,8 +197,11 @@ __device__ __forceinline__ void eval_tile(const Rows& x, const Rows& y, int whic
   const bool longrows = E.dmax >= KW;
   const int rd = longrows ? (isy ? y.deg_x : x.deg_x)[row] : 0;
   bool first = true;
-  for (int ch = longrows ? E.dmax / KW : 0; ch >= 0; --ch) {
-    if (longrows && first && ch && __ballot(!past && rd >= ch * KW) == 0ull) continue;
+  for (int ch = part >= 0 ? part : longrows ? E.dmax / KW : 0; ch >= 0; --ch) {
+    if (longrows && first && ch && __ballot(!past && rd >= ch * KW) == 0ull) {
+      if (part >= 0) return false;
+      continue;
+    }
     const int c0 = ch * KW + (KW / 4) * g;
     const __attribute__((address_space(1))) u32x4* src =
         (const __attribute__((address_space(1))) u32x4*)(gmem(rows) + (size_t)row * lp + c0);
@@ -250,10 +262,13 @@ __device__ __forceinline__ void eval_tile(const Rows& x, const Rows& y, int whic
       const u2 hi = __builtin_amdgcn_permlane16_swap(s02.y, s13.y, false, false);
       const int32_t v[4] = {(int32_t)lo.x, (int32_t)lo.y, (int32_t)hi.x, (int32_t)hi.y};
 #pragma unroll
-      for (int r = 0; r < 4; ++r) out[4 * j + r] = first ? v[r] : sdot2(out[4 * j + r], E.apw, v[r], E.one, q);
+      for (int r = 0; r < 4; ++r)
+        out[4 * j + r] = part >= 0 || first ? v[r] : sdot2(out[4 * j + r], E.apw, v[r], E.one, q);
     }
+    if (part >= 0) break;
     first = false;
   }
+  return true;
 }
 
 // f(0), ..., f(N - 1) with compile-time indices: the register arrays are only
@@ -596,20 +611,35 @@ __device__ __forceinline__ void ee_eval(const JobDev& J, int k, int blk, TablesD
   constexpr int T = C / 16, RJ = (C % 16) / 4;
   static_assert(C % 16 <= 8 && C % 4 == 0, "the rest of both arrays fits one tile");
   sfor<C>(EE_IDX(i) { X[i] = Y[i] = own_reg(0); });  // (opaque zeros: a fill would keep the array whole)
+  // At capacity 24 the pieces of longer rows are the outer loop and join in the
+  // arrays themselves: a tile's values need not be kept over its matrix products,
+  // which fits the kernel into its 128 registers without scratch.  (The others have
+  // registers to spare, and their code should not grow.)
+  constexpr bool OUTER = C == 24;
+  const int top = OUTER && E.dmax >= KW ? E.dmax / KW : 0;
+  auto join = [&](int32_t& z, int32_t v, bool add) __attribute__((always_inline)) {
+    if (OUTER && add)
+      z = sdot2(z, E.apw, v, E.one, own_mod(q));
+    else
+      z = own_reg(v);
+  };
+#pragma unroll 1
+  for (int part = top; part >= 0; --part)
 #pragma unroll 1
   for (int id = 0; id < 2 * T + (RJ ? 1 : 0); ++id) {
     const int which = id == 2 * T ? 2 : id >= T ? 1 : 0, tau = which == 2 ? T : which ? id - T : id;
     if (16 * tau > (which == 0 ? x.deg : which == 1 ? y.deg : max(x.deg, y.deg))) continue;
     int32_t o[16];
-    eval_tile<KW, RJ ? RJ : 1>(x, y, which, 16 * tau, E, o, q);
+    if (!eval_tile<KW, RJ ? RJ : 1>(x, y, which, 16 * tau, OUTER ? part : -1, E, o, q)) continue;
+    const bool add = OUTER && part < top;
     sfor<T>(EE_IDX(t) {
-      if (id == t) sfor<16>(EE_IDX(i) { X[16 * t + i] = own_reg(o[i]); });
-      if (id == T + t) sfor<16>(EE_IDX(i) { Y[16 * t + i] = own_reg(o[i]); });
+      if (id == t) sfor<16>(EE_IDX(i) { join(X[16 * t + i], o[i], add); });
+      if (id == T + t) sfor<16>(EE_IDX(i) { join(Y[16 * t + i], o[i], add); });
     });
     if constexpr (RJ > 0) {
       if (id == 2 * T) {
-        sfor<4 * RJ>(EE_IDX(i) { X[16 * T + i] = own_reg(o[i]); });
-        sfor<4 * RJ>(EE_IDX(i) { Y[16 * T + i] = own_reg(o[4 * RJ + i]); });
+        sfor<4 * RJ>(EE_IDX(i) { join(X[16 * T + i], o[i], add); });
+        sfor<4 * RJ>(EE_IDX(i) { join(Y[16 * T + i], o[4 * RJ + i], add); });
       }
     }
   }
