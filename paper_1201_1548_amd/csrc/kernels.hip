@@ -11,16 +11,19 @@
 //   k_schur       (c) the same elimination by the Schur algorithm on the
 //                 displacement generators, one wave per (prime, point)
 //   k_psc         principal subresultant coefficients mod p, one lane per point
-//   k_interp      (d) interpolation per prime, nodes a = 0..D-1
+//                 (along normal sequences in registers: ee.hip)
+//   k_interp      (d) interpolation per prime, nodes a = 0..D-1 (on the nodes
+//                 2^a: interp_geo.hip)
 //   k_interp_mfma (d) interpolation of a batch sharing the nodes, int8 matrix
 //                 cores (value digit planes written by the evaluation
 //                 kernels, V^{-1} by k_vinv)
 //   k_invfact     table of 1/n! mod p (set-up)
-//   k_crt_mfma    (e) explicit CRT straight to limbs, int8 matrix cores
+//   k_crt_mfma    (e) explicit CRT straight to limbs, int8 matrix cores, up to 128
+//                 primes (tables and larger counts: crt.hip)
 //   k_mrc         (e) mixed-radix (Garner) digits per coefficient
 //   k_limbs_sum / k_limbs_carry   (e) digits -> two's-complement limbs
 //   k_fused       every stage after the reduction in one persistent launch
-//   k_gcd_p / k_fiber_chain   gcd mod p, the N^- / N^+ degree chain
+// (k_gcd_p and k_fiber_chain are in gcd_kernels.hip.)
 //
 // Every kernel is batch-native: an array of per-job first-block indices maps
 // each block to its job (find_job), so a single job is a batch of one.
