@@ -3,11 +3,11 @@
 #include <algorithm>
 #include <chrono>
 #include <cstring>
-#include <type_traits>
 
 #include "engine.hpp"
 #include "kernels.hpp"
 #include "scratch.hpp"
+#include "seqhash.hpp"
 #include "tables.hpp"
 
 namespace bires {
@@ -131,27 +131,6 @@ static int validate(const JobIn& jb, bool need_out) {
   } while (0)
 
 namespace {
-// FNV-1a hash of the arguments of a device call sequence.
-struct SeqHash {
-  uint64_t h = 1469598103934665603ull;
-  void bytes(const void* p, size_t n) {
-    const unsigned char* c = (const unsigned char*)p;
-    for (size_t i = 0; i < n; ++i) h = (h ^ c[i]) * 1099511628211ull;
-  }
-  template <class T>
-  void one(const T& v) {
-    static_assert(std::is_arithmetic<T>::value || std::is_pointer<T>::value || std::is_enum<T>::value,
-                  "hash scalars and pointers only");
-    bytes(&v, sizeof v);
-  }
-  // a plain struct of pointers and counts, value-initialised (zero padding)
-  void one(const FusedPlan& F) { bytes(&F, sizeof F); }
-  template <class... A>
-  void add(const A&... a) {
-    (one(a), ...);
-  }
-};
-
 // Host time per phase of a batched call (microseconds), accumulated into the
 // context when timing is enabled.
 struct HostClock {
@@ -963,7 +942,7 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
     meta_mapped = (const uint32_t*)m;
   }
   auto seq = [&](bool run, SeqHash& sg) -> int {
-    sg.add(st, D0, meta_begin, meta_end, (const void*)meta_mapped, (const void*)etab.qpow, etab.geo_D);
+    sg.add(st, D0, meta_begin, meta_end, (const void*)meta_mapped, etab);  // (etab holds cx->tab's)
     for (int c = 0; c < GEO_CLASSES; ++c) sg.add(nb_of(K_GE0 + c), gmax[c]);
     if (run && meta_end > meta_begin) {
       if (noalloc)
@@ -981,7 +960,8 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
       // residues through the scalar cache
       sg.add(nb_of(K_RED), maxP);
       if (run && nb_of(K_RED)) launch_reduce(d_jobs, st_of(K_RED), nj, nb_of(K_RED), maxP, cx->tab, st);
-      sg.add(F, fC, fKS, f_lds, f_blocks);
+      sg.bytes(&F, sizeof F);  // (pointers and counts, value-initialised: the padding is zero)
+      sg.add(fC, fKS, f_lds, f_blocks);
       if (run && timing) DEV(hipEventRecord(ev0, st));
       if (run) launch_fused(fC, fKS, F, f_lds, f_blocks, cx->tab, st);
       if (run && timing) DEV(hipEventRecord(ev1, st));
