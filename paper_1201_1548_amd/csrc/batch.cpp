@@ -545,6 +545,7 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
   {
     int lastP = -1, lastLM = 0;
     const uint32_t* lastd = nullptr;
+    bool asked = false;
     std::vector<int> cls(nj, -1);
     long long small_blocks = 0;
     int small_top = -1;
@@ -555,15 +556,17 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
       if (c < 0) continue;
       if (Pi != lastP) {  // consecutive jobs mostly share P
         lastP = Pi;
-        // allocation-free calls use only operand tables that already exist
-        lastd = noalloc ? crt_device_cached(cx, lastP, &lastLM) : crt_device(cx, lastP, st, &lastLM);
+        lastLM = radix_limbs(Pi);
+        asked = false;
       }
+      if (!crt_fits(Pi, lastLM, x.Lout, cx->lds_per_block)) continue;
+      // allocation-free calls use only operand tables that already exist
+      if (!asked) lastd = noalloc ? crt_device_cached(cx, Pi) : crt_device(cx, Pi, st);
+      asked = true;
       if (!lastd) {
         use_crt = false;
         continue;
       }
-      if (c == CRT_BIG && (crt_big_lds_bytes(Pi, lastLM) > cx->lds_per_block || !crt_big_limbs_ok(lastLM, x.Lout)))
-        continue;
       crt[i] = {lastd, lastLM};
       cls[i] = c;
       if (c != CRT_BIG) {

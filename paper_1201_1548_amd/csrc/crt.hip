@@ -310,6 +310,11 @@ size_t crt_big_lds_bytes(int P, int LM) { return cb_layout(P, LM).bytes; }
 // The range check keeps CB_TAIL limbs from the end of the output row on.
 bool crt_big_limbs_ok(int LM, int lcap) { return 8 * column_tiles(LM) - (lcap & ~3) <= CB_TAIL; }
 
+bool crt_fits(int P, int LM, int lcap, size_t lds_per_block) {
+  const int c = crt_class(P);
+  return c >= 0 && (c != CRT_BIG || (crt_big_lds_bytes(P, LM) <= lds_per_block && crt_big_limbs_ok(LM, lcap)));
+}
+
 void launch_crt_big(const JobDev* jobs, const int* starts, int nj, int nblocks, size_t lds, TablesDev tab,
                     hipStream_t s) {
   hipLaunchKernelGGL(k_crt_big, dim3(nblocks), dim3(64 * CBW), lds, s, jobs, starts, nj, tab);

@@ -142,39 +142,34 @@ static int init_context(Context& cx) {
   return BIRES_OK;
 }
 
-const uint32_t* crt_device(Context* cx, int P, hipStream_t st, int* LM) {
+const uint32_t* crt_device(Context* cx, int P, hipStream_t st) {
   constexpr size_t kLimit = (size_t)1 << 30;
   std::lock_guard<std::mutex> lk(cx->crt_mu);
   auto it = cx->crt.find(P);
-  if (it == cx->crt.end()) {
-    const uint32_t* M = &host_tables().pi[(size_t)P * (P + 1) / 2];
-    int lm = P + 1;
-    while (lm > 1 && M[lm - 1] == 0u) --lm;
-    const size_t bytes = crt_table_words(P, lm) * sizeof(uint32_t);
-    if (cx->crt_total + bytes > kLimit) return nullptr;
-    uint32_t* d = nullptr;
-    if (hipMalloc(&d, bytes) != hipSuccess) {
-      (void)hipGetLastError();
-      return nullptr;
-    }
-    launch_crt_tables(cx->tab, P, lm, d, st);
-    if (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess) {
-      (void)hipFree(d);
-      return nullptr;
-    }
-    cx->crt_total += bytes;
-    it = cx->crt.emplace(P, std::make_pair((const uint32_t*)d, lm)).first;
+  if (it != cx->crt.end()) return it->second;
+  const int LM = radix_limbs(P);
+  const bool small = P <= CRT_SMALL_PRIMES;
+  const size_t bytes = crt_table_words(P, LM) * sizeof(uint32_t);
+  if (!small && cx->crt_total + bytes > kLimit) return nullptr;
+  uint32_t* d = nullptr;
+  if (hipMalloc(&d, bytes) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
   }
-  *LM = it->second.second;
-  return it->second.first;
+  launch_crt_tables(cx->tab, P, LM, d, st);
+  if (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess) {
+    (void)hipFree(d);
+    return nullptr;
+  }
+  if (!small) cx->crt_total += bytes;
+  cx->crt.emplace(P, d);
+  return d;
 }
 
-const uint32_t* crt_device_cached(Context* cx, int P, int* LM) {
+const uint32_t* crt_device_cached(Context* cx, int P) {
   std::lock_guard<std::mutex> lk(cx->crt_mu);
   auto it = cx->crt.find(P);
-  if (it == cx->crt.end()) return nullptr;
-  *LM = it->second.second;
-  return it->second.first;
+  return it == cx->crt.end() ? nullptr : it->second;
 }
 
 bool graph_launch(Context* cx, uint64_t key, hipStream_t st) {

@@ -94,8 +94,8 @@ struct Context {
   double host_us[BIRES_HOST_PHASES] = {0};
   int64_t host_calls = 0;
   std::mutex crt_mu;
-  size_t crt_total = 0;                                 // bytes of the CRT tables
-  std::map<int, std::pair<const uint32_t*, int>> crt;  // P -> (device table, LM)
+  size_t crt_total = 0;                                 // bytes of the CRT tables above CRT_SMALL_PRIMES
+  std::map<int, const uint32_t*> crt;                   // P -> device table
   std::atomic<int> eval_mode{BIRES_EVAL_AUTO};           // evaluation + elimination kernel (BIRES_EVAL_*)
   std::atomic<long long> schur_instances{0}, schur_fallbacks{0};  // Schur kernel statistics
   std::atomic<bool> graphs{false};                       // replay device sequences as captured graphs
@@ -170,11 +170,14 @@ bool geo_tables_device(Context* cx, int D, int P, hipStream_t st, TablesDev* tab
 // for all).
 void pow_planes_device(Context* cx, int D, int P, hipStream_t st, TablesDev* tab);
 
-// The explicit CRT's tables of P primes, built on first use (on stream st, which
-// is then synchronised) and kept; nullptr above 1 GiB in all or on failure.
-const uint32_t* crt_device(Context* cx, int P, hipStream_t st, int* LM);
+// The explicit CRT's tables of P primes (limbs of the modulus: radix_limbs),
+// built on first use (on stream st, which is then synchronised) and kept;
+// nullptr on failure, or when those of the counts above CRT_SMALL_PRIMES would
+// exceed 1 GiB in all (the others take 14 MiB at most).  A caller asks only
+// for counts whose launch fits (crt_fits).
+const uint32_t* crt_device(Context* cx, int P, hipStream_t st);
 // The same when it already exists, else nullptr (never allocates).
-const uint32_t* crt_device_cached(Context* cx, int P, int* LM);
+const uint32_t* crt_device_cached(Context* cx, int P);
 
 // Autotuning key of a planned batch: log2-buckets of the total (prime, point)
 // instances, of the largest m + n and of the largest prime count.

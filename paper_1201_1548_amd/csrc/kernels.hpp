@@ -119,6 +119,11 @@ int crt_class_primes(int cls);
 // largest of the launch), output rows with crt_big_limbs_ok.
 size_t crt_big_lds_bytes(int P, int LM);
 bool crt_big_limbs_ok(int LM, int lcap);
+// Whether the kernel of P's class takes a job of P primes (a modulus of LM limbs)
+// with output rows of lcap limbs; of the small classes the launch's LDS remains
+// to be checked.  No tables are needed for the answer, and none should be
+// built before it.
+bool crt_fits(int P, int LM, int lcap, size_t lds_per_block);
 void launch_crt_big(const JobDev* jobs, const int* starts, int nj, int nblocks, size_t lds, TablesDev tab,
                     hipStream_t s);
 // Explicit CRT constants of the first P primes, M = prod_{k<P} p_k: one

@@ -122,4 +122,11 @@ const HostTables& host_tables() {
   return t;
 }
 
+int radix_limbs(int P) {
+  const uint32_t* M = &host_tables().pi[(size_t)P * (P + 1) / 2];
+  int n = P + 1;
+  while (n > 1 && M[n - 1] == 0u) --n;
+  return n;
+}
+
 }  // namespace bires

@@ -29,5 +29,7 @@ ModP make_modp(uint32_t p);
 void mrc_tables(const std::vector<ModP>& primes, std::vector<uint32_t>& gm, std::vector<uint32_t>& cm,
                 std::vector<uint32_t>& pm, std::vector<uint32_t>& pi);
 const HostTables& host_tables();
+// Limbs of prod_{k<P} p_k, P < MAX_PRIMES.
+int radix_limbs(int P);
 
 }  // namespace bires
