@@ -233,6 +233,34 @@ bool interp_tables_device(Context* cx, int blocks, int primes, hipStream_t st, c
   return true;
 }
 
+// Sets *tab to the geometric nodes' tables of P primes and Dm indices at d.
+static void set_geo(const void* d, int Dm, int P, TablesDev* tab) {
+  const size_t n = (size_t)P * Dm;
+  const uint32_t* w = (const uint32_t*)d;
+  tab->qpow = w;
+  tab->geo_invu = w + n;
+  tab->geo_w = w + 2 * n;
+  tab->geo_A = (const int8_t*)(w + 3 * n);
+  tab->geo_D = Dm;
+}
+
+// Those tables in memory of their own, built on st; nullptr on failure.
+static void* build_geo(const ModP* primes, int Dm, int P, hipStream_t st) {
+  uint8_t* d = nullptr;
+  if (hipMalloc((void**)&d, geo_table_bytes(Dm, P)) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  const size_t n = (size_t)P * Dm;
+  uint32_t* w = (uint32_t*)d;
+  launch_geo_tables(primes, Dm, P, w, w + n, w + 2 * n, (int8_t*)(w + 3 * n), st);
+  if (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess) {
+    (void)hipFree(d);
+    return nullptr;
+  }
+  return d;
+}
+
 bool geo_tables_device(Context* cx, int D, int P, hipStream_t st, TablesDev* tab) {
   constexpr size_t kOne = (size_t)512 << 20, kAll = (size_t)1 << 30;
   std::lock_guard<std::mutex> lk(cx->geo_mu);
@@ -250,28 +278,29 @@ bool geo_tables_device(Context* cx, int D, int P, hipStream_t st, TablesDev* tab
     if (geo_table_bytes(Dm, Pm) > kOne || total + geo_table_bytes(Dm, Pm) > kAll) Dm = D0, Pm = P0;
     const size_t bytes = geo_table_bytes(Dm, Pm);
     if (bytes > kOne || total + bytes > kAll) return false;
-    uint8_t* d = nullptr;
-    if (hipMalloc((void**)&d, bytes) != hipSuccess) {
-      (void)hipGetLastError();
-      return false;
-    }
-    const size_t n = (size_t)Pm * Dm;
-    uint32_t* w = (uint32_t*)d;
-    launch_geo_tables(cx->tab.primes, Dm, Pm, w, w + n, w + 2 * n, (int8_t*)(w + 3 * n), st);
-    if (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess) {
-      (void)hipFree(d);
-      return false;
-    }
+    void* d = build_geo(cx->tab.primes, Dm, Pm, st);
+    if (!d) return false;
     cx->geo.push_back({d, Dm, Pm, bytes});
     hit = &cx->geo.back();
   }
-  const size_t n = (size_t)hit->P * hit->D;
-  const uint32_t* w = (const uint32_t*)hit->p;
-  tab->qpow = w;
-  tab->geo_invu = w + n;
-  tab->geo_w = w + 2 * n;
-  tab->geo_A = (const int8_t*)(w + 3 * n);
-  tab->geo_D = hit->D;
+  set_geo(hit->p, hit->D, hit->P, tab);
+  return true;
+}
+
+bool geo_tables_of_prime(Context* cx, int D, int k, hipStream_t st, TablesDev* tab) {
+  constexpr size_t kAll = (size_t)64 << 20;
+  std::lock_guard<std::mutex> lk(cx->geo_mu);
+  const int Dm = (D + 255) & ~255;
+  auto it = cx->geo_one.find({k, Dm});
+  if (it == cx->geo_one.end()) {
+    const size_t bytes = geo_table_bytes(Dm, 1);
+    if (cx->geo_one_total + bytes > kAll) return false;
+    void* d = build_geo(cx->tab.primes + k, Dm, 1, st);
+    if (!d) return false;
+    cx->geo_one_total += bytes;
+    it = cx->geo_one.emplace(std::make_pair(k, Dm), d).first;
+  }
+  set_geo(it->second, Dm, 1, tab);
   return true;
 }
 

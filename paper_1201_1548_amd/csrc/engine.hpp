@@ -117,6 +117,8 @@ struct Context {
   };
   std::mutex geo_mu;                                    // tables of the geometric nodes (geo_tables_device)
   std::vector<GeoTable> geo;
+  std::map<std::pair<int, int>, void*> geo_one;         // (prime, indices) -> the same of one prime
+  size_t geo_one_total = 0;                             // under geo_mu
   struct PowTable {
     const int8_t* p;
     bool geo;
@@ -165,6 +167,9 @@ bool interp_tables_device(Context* cx, int blocks, int primes, hipStream_t st, c
 // and 1 GiB in all; never freed, calls in flight may read them).  False when
 // they would not fit or the build failed: the call then uses the nodes 0..D-1.
 bool geo_tables_device(Context* cx, int D, int P, hipStream_t st, TablesDev* tab);
+// The same for table prime k alone, as prime 0 of *tab (the tables shifted to
+// it): at most 622 KB, kept apart from the batches' tables, 64 MiB in all.
+bool geo_tables_of_prime(Context* cx, int D, int k, hipStream_t st, TablesDev* tab);
 // Fills tab->pow_planes for at least D points and P primes on the nodes tab is set
 // up for; leaves it null when the table would exceed its limits (32 MiB, 256 MiB
 // for all).

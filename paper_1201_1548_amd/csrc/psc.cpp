@@ -81,13 +81,6 @@ TablesDev shifted(const TablesDev& t, int k) {
   s.invfact += (size_t)k * t.dmax;
   s.inv_p += k;
   s.K -= k;
-  if (s.qpow) {
-    const size_t o = (size_t)k * t.geo_D;
-    s.qpow += o;
-    s.geo_invu += o;
-    s.geo_w += o;
-    s.geo_A += 64 * o;
-  }
   return s;
 }
 
@@ -193,9 +186,8 @@ static int psc_device(Context* cx, const HostJob& h, int kind, int kp, int kmax,
     is[i] = i;
   }
   is[K] = K;
-  TablesDev base = cx->tab;
-  const bool geo = geo_tables_device(cx, D, kp + 1, st, &base);
-  const TablesDev tab = shifted(base, kp);
+  TablesDev tab = shifted(cx->tab, kp);
+  const bool geo = geo_tables_of_prime(cx, D, kp, st, &tab);
   r.queued.st = st;
   r.queued.on = true;
   DEV(hipMemcpyAsync(r.ws.p, H, up_end, hipMemcpyHostToDevice, st));
