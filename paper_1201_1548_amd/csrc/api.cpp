@@ -274,7 +274,7 @@ int bires_set_graphs(int enable) {
   cx->graphs = enable != 0;
   if (!cx->graphs && !cx->graph_cache.empty()) {
     if (hipDeviceSynchronize() != hipSuccess) return BIRES_EDEVICE;
-    for (auto& kv : cx->graph_cache) (void)hipGraphExecDestroy(kv.second);
+    for (auto& kv : cx->graph_cache) (void)hipGraphExecDestroy(kv.second.exec);
     cx->graph_cache.clear();
     cx->graph_order.clear();
   }

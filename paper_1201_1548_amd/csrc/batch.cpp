@@ -195,6 +195,7 @@ struct PendingBatch {
   std::vector<int> rd_off;
   bool spec = false, spec_ok = false, fused = false, timing = false;
   std::shared_ptr<DevImage> image;  // statistics the reused plans were made from
+  TableRefs tables;                 // tables that the launches read
   size_t o_scan0 = 0, scan_words = 0;
   int32_t* h_flags = nullptr;
   long long schur_instances = 0;  // (prime, point) instances on the Schur kernel
@@ -543,9 +544,12 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
   int crtP[CRT_CLASSES] = {0}, crtL[CRT_CLASSES] = {0};         // largest prime count, limb capacity per class
   size_t crt_lds[CRT_CLASSES] = {0};
   {
-    int lastP = -1, lastLM = 0;
-    const uint32_t* lastd = nullptr;
-    bool asked = false;
+    struct ByCount {  // once per prime count
+      int LM = 0;
+      bool asked = false;
+      const uint32_t* d = nullptr;
+    };
+    std::vector<ByCount> counts(std::min(maxP, CRT_MAX_PRIMES) + 1);
     std::vector<int> cls(nj, -1);
     long long small_blocks = 0;
     int small_top = -1;
@@ -554,20 +558,17 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
       if (x.status || !x.active) continue;
       const int Pi = x.pl.P, c = crt_class(Pi);
       if (c < 0) continue;
-      if (Pi != lastP) {  // consecutive jobs mostly share P
-        lastP = Pi;
-        lastLM = radix_limbs(Pi);
-        asked = false;
-      }
-      if (!crt_fits(Pi, lastLM, x.Lout, cx->lds_per_block)) continue;
+      ByCount& t = counts[Pi];
+      if (!t.LM) t.LM = radix_limbs(Pi);
+      if (!crt_fits(Pi, t.LM, x.Lout, cx->lds_per_block)) continue;
       // allocation-free calls use only operand tables that already exist
-      if (!asked) lastd = noalloc ? crt_device_cached(cx, Pi) : crt_device(cx, Pi, st);
-      asked = true;
-      if (!lastd) {
+      if (!t.asked) t.d = noalloc ? crt_device_cached(cx, Pi, &P->tables) : crt_device(cx, Pi, st, &P->tables);
+      t.asked = true;
+      if (!t.d) {
         use_crt = false;
         continue;
       }
-      crt[i] = {lastd, lastLM};
+      crt[i] = {t.d, t.LM};
       cls[i] = c;
       if (c != CRT_BIG) {
         const int rows = crt_rows_per_block(crt_class_primes(c));
@@ -633,10 +634,11 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
   // every other batch: the geometric nodes where their tables fit, else the
   // nodes 0..D-1 with the block tables of the per-(job, prime) kernel
   TablesDev etab = cx->tab;  // tables of the evaluation and interpolation launches
+  TableRefs by_value;        // those of them that a captured graph keeps
   // (the Schur schedule, whose fallback statistics count vanishing pivots at
   // the points 0..D-1, and the persistent launch keep those nodes)
   const bool geo = group.empty() && !debug && !noalloc && !fused && !schur && instances > 0 &&
-                   geo_tables_device(cx, maxD, maxP, st, &etab);
+                   geo_tables_device(cx, maxD, maxP, st, &etab, &by_value);
   if (group.empty() && !geo && !debug && !noalloc &&
       !interp_tables_device(cx, interp_table_blocks(maxD), maxP, st, &itW, &itQ, &itNB)) {
     itW = itQ = nullptr;
@@ -649,8 +651,9 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
     for (int i = 0; i < nj; ++i)
       if (starts[K_RG0][i + 1] != starts[K_RG0][i] || starts[K_RG0 + 1][i + 1] != starts[K_RG0 + 1][i])
         rD = std::max(rD, w[i].pl.D), rP = std::max(rP, w[i].pl.P);
-    pow_planes_device(cx, rD, rP, st, &etab);
+    pow_planes_device(cx, rD, rP, st, &etab, &by_value);
   }
+  P->tables.insert(P->tables.end(), by_value.begin(), by_value.end());
   const int gDp = (gD + 31) & ~31, gNp = ((int)group.size() + 31) & ~31;
   const size_t o_yp = group.empty() ? 0 : ws.take((size_t)4 * gNp * gDp * gP);
   // persistent fused launch: the evaluation's block lists (register Euclid at
@@ -1051,7 +1054,7 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
         hipGraphExec_t exec = nullptr;
         const bool ended = hipStreamEndCapture(st, &g) == hipSuccess;
         if (e == BIRES_OK && ended && g && hipGraphInstantiate(&exec, g, nullptr, nullptr, 0) == hipSuccess)
-          launched = graph_store_launch(cx, sig.h, exec, st);
+          launched = graph_store_launch(cx, sig.h, exec, by_value, st);
         if (g) (void)hipGraphDestroy(g);
         (void)hipGetLastError();
       }

@@ -49,6 +49,7 @@ void* Pool::alloc(size_t bytes) {
   if (e != hipSuccess) {
     (void)hipGetLastError();
     trim();
+    if (on_full_) on_full_();
     e = pinned_ ? hipHostMalloc(&p, c, hipHostMallocDefault) : hipMalloc(&p, c);
     if (e != hipSuccess) {
       (void)hipGetLastError();
@@ -90,6 +91,8 @@ void Pool::trim() {
 
 // ---------------------------------------------------------------------------
 // context
+
+static void release_tables(Context* cx);
 
 static int init_context(Context& cx) {
   int dev = 0;
@@ -138,65 +141,103 @@ static int init_context(Context& cx) {
     const int e = scratch_address(&cx.scratch, &cx.scratch_bytes);
     if (e) return e;
   }
+  cx.dev.set_on_full([&cx] { release_tables(&cx); });
   tune_load(&cx);
   return BIRES_OK;
 }
 
-const uint32_t* crt_device(Context* cx, int P, hipStream_t st) {
-  constexpr size_t kLimit = (size_t)1 << 30;
-  std::lock_guard<std::mutex> lk(cx->crt_mu);
-  auto it = cx->crt.find(P);
-  if (it != cx->crt.end()) return it->second;
-  const int LM = radix_limbs(P);
-  const bool small = P <= CRT_SMALL_PRIMES;
-  const size_t bytes = crt_table_words(P, LM) * sizeof(uint32_t);
-  if (!small && cx->crt_total + bytes > kLimit) return nullptr;
-  uint32_t* d = nullptr;
-  if (hipMalloc(&d, bytes) != hipSuccess) {
+// Device memory of `bytes` filled by launch(p) on st; null on failure.
+template <class F>
+static TableRef build_table(size_t bytes, hipStream_t st, F launch) {
+  TableRef t = std::make_shared<DevTable>();
+  if (hipMalloc(&t->p, bytes) != hipSuccess) {
     (void)hipGetLastError();
+    t->p = nullptr;
     return nullptr;
   }
-  launch_crt_tables(cx->tab, P, LM, d, st);
-  if (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess) {
-    (void)hipFree(d);
-    return nullptr;
-  }
-  if (!small) cx->crt_total += bytes;
-  cx->crt.emplace(P, d);
-  return d;
+  launch(t->p);
+  if (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess) return nullptr;
+  return t;
 }
 
-const uint32_t* crt_device_cached(Context* cx, int P) {
-  std::lock_guard<std::mutex> lk(cx->crt_mu);
-  auto it = cx->crt.find(P);
-  return it == cx->crt.end() ? nullptr : it->second;
+// Captured graphs that read a table that is no longer handed out: no later call
+// has their signature, and they would keep the table's memory.
+static void graph_forget(Context* cx, const TableRefs& gone) {
+  if (gone.empty()) return;
+  std::lock_guard<std::mutex> lk(cx->graph_mu);
+  bool waited = false;
+  for (size_t i = 0; i < cx->graph_order.size();) {
+    const auto it = cx->graph_cache.find(cx->graph_order[i]);
+    bool reads = false;
+    for (const TableRef& t : it->second.tables) reads |= std::find(gone.begin(), gone.end(), t) != gone.end();
+    if (!reads) {
+      ++i;
+      continue;
+    }
+    if (!waited && hipDeviceSynchronize() != hipSuccess) return;  // rare, as in graph_store_launch
+    waited = true;
+    (void)hipGraphExecDestroy(it->second.exec);
+    cx->graph_cache.erase(it);
+    cx->graph_order.erase(cx->graph_order.begin() + i);
+  }
+}
+
+// Gives back every table that no call in flight reads, but for the small CRT tables.
+static void release_tables(Context* cx) {
+  TableRefs gone;
+  for (TableCache<DevTable>* c : {&cx->geo, &cx->geo_one, &cx->pow, &cx->crt_big}) c->clear(&gone);
+  graph_forget(cx, gone);
+}
+
+const uint32_t* crt_device(Context* cx, int P, hipStream_t st, TableRefs* refs) {
+  const int LM = radix_limbs(P);
+  const size_t bytes = crt_table_words(P, LM) * sizeof(uint32_t);
+  TableRefs gone;
+  const auto t = (P <= CRT_SMALL_PRIMES ? cx->crt_small : cx->crt_big)
+                     .get(P, 0, 0, false, [&](int, int) { return bytes; },
+                          [&](int, int) {
+                            return build_table(bytes, st, [&](void* d) {
+                              launch_crt_tables(cx->tab, P, LM, (uint32_t*)d, st);
+                            });
+                          },
+                          &gone);
+  if (!t.mem) return nullptr;
+  refs->push_back(t.mem);
+  return (const uint32_t*)t.mem->p;
+}
+
+const uint32_t* crt_device_cached(Context* cx, int P, TableRefs* refs) {
+  const auto t = (P <= CRT_SMALL_PRIMES ? cx->crt_small : cx->crt_big).look(P, 0, 0);
+  if (!t.mem) return nullptr;
+  refs->push_back(t.mem);
+  return (const uint32_t*)t.mem->p;
 }
 
 bool graph_launch(Context* cx, uint64_t key, hipStream_t st) {
   std::lock_guard<std::mutex> lk(cx->graph_mu);
   auto it = cx->graph_cache.find(key);
   if (it == cx->graph_cache.end()) return false;
-  if (hipGraphLaunch(it->second, st) != hipSuccess) return false;
+  if (hipGraphLaunch(it->second.exec, st) != hipSuccess) return false;
   cx->graph_replays++;
   return true;
 }
 
-bool graph_store_launch(Context* cx, uint64_t key, hipGraphExec_t exec, hipStream_t st) {
+bool graph_store_launch(Context* cx, uint64_t key, hipGraphExec_t exec, const TableRefs& tables, hipStream_t st) {
   std::lock_guard<std::mutex> lk(cx->graph_mu);
   auto it = cx->graph_cache.find(key);
   if (it != cx->graph_cache.end()) {  // another thread stored the same sequence
     (void)hipGraphExecDestroy(exec);
-    exec = it->second;
+    exec = it->second.exec;
   } else {
     if (cx->graph_order.size() >= 32) {
       // rare: wait for every launch before destroying the oldest executable
       (void)hipDeviceSynchronize();
       const uint64_t old = cx->graph_order.front();
       cx->graph_order.erase(cx->graph_order.begin());
-      (void)hipGraphExecDestroy(cx->graph_cache[old]);
+      (void)hipGraphExecDestroy(cx->graph_cache[old].exec);
       cx->graph_cache.erase(old);
     }
-    cx->graph_cache[key] = exec;
+    cx->graph_cache[key] = CachedGraph{exec, tables};
     cx->graph_order.push_back(key);
     cx->graph_captures++;
   }
@@ -244,100 +285,52 @@ static void set_geo(const void* d, int Dm, int P, TablesDev* tab) {
   tab->geo_D = Dm;
 }
 
-// Those tables in memory of their own, built on st; nullptr on failure.
-static void* build_geo(const ModP* primes, int Dm, int P, hipStream_t st) {
-  uint8_t* d = nullptr;
-  if (hipMalloc((void**)&d, geo_table_bytes(Dm, P)) != hipSuccess) {
-    (void)hipGetLastError();
-    return nullptr;
-  }
-  const size_t n = (size_t)P * Dm;
-  uint32_t* w = (uint32_t*)d;
-  launch_geo_tables(primes, Dm, P, w, w + n, w + 2 * n, (int8_t*)(w + 3 * n), st);
-  if (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess) {
-    (void)hipFree(d);
-    return nullptr;
-  }
-  return d;
+// Those tables in memory of their own, built on st; null on failure.
+static TableRef build_geo(const ModP* primes, int Dm, int P, hipStream_t st) {
+  return build_table(geo_table_bytes(Dm, P), st, [&](void* d) {
+    const size_t n = (size_t)P * Dm;
+    uint32_t* w = (uint32_t*)d;
+    launch_geo_tables(primes, Dm, P, w, w + n, w + 2 * n, (int8_t*)(w + 3 * n), st);
+  });
 }
 
-bool geo_tables_device(Context* cx, int D, int P, hipStream_t st, TablesDev* tab) {
-  constexpr size_t kOne = (size_t)512 << 20, kAll = (size_t)1 << 30;
-  std::lock_guard<std::mutex> lk(cx->geo_mu);
-  const Context::GeoTable* hit = nullptr;
-  size_t total = 0;
-  int Dm = (D + 255) & ~255, Pm = std::min((P + 31) & ~31, cx->tab.K);
-  for (const auto& g : cx->geo) {
-    total += g.bytes;
-    if (g.D >= D && g.P >= P && (!hit || g.bytes < hit->bytes)) hit = &g;
-  }
-  if (!hit) {
-    // large enough for the earlier calls too, if that fits, else for this one
-    const int D0 = Dm, P0 = Pm;
-    for (const auto& g : cx->geo) Dm = std::max(Dm, g.D), Pm = std::max(Pm, g.P);
-    if (geo_table_bytes(Dm, Pm) > kOne || total + geo_table_bytes(Dm, Pm) > kAll) Dm = D0, Pm = P0;
-    const size_t bytes = geo_table_bytes(Dm, Pm);
-    if (bytes > kOne || total + bytes > kAll) return false;
-    void* d = build_geo(cx->tab.primes, Dm, Pm, st);
-    if (!d) return false;
-    cx->geo.push_back({d, Dm, Pm, bytes});
-    hit = &cx->geo.back();
-  }
-  set_geo(hit->p, hit->D, hit->P, tab);
+bool geo_tables_device(Context* cx, int D, int P, hipStream_t st, TablesDev* tab, TableRefs* refs) {
+  TableRefs gone;
+  const auto t = cx->geo.get(0, (D + 255) & ~255, std::min((P + 31) & ~31, cx->tab.K), true, geo_table_bytes,
+                             [&](int Dm, int Pm) { return build_geo(cx->tab.primes, Dm, Pm, st); }, &gone);
+  graph_forget(cx, gone);
+  if (!t.mem) return false;
+  refs->push_back(t.mem);
+  set_geo(t.mem->p, t.a, t.b, tab);
   return true;
 }
 
-bool geo_tables_of_prime(Context* cx, int D, int k, hipStream_t st, TablesDev* tab) {
-  constexpr size_t kAll = (size_t)64 << 20;
-  std::lock_guard<std::mutex> lk(cx->geo_mu);
-  const int Dm = (D + 255) & ~255;
-  auto it = cx->geo_one.find({k, Dm});
-  if (it == cx->geo_one.end()) {
-    const size_t bytes = geo_table_bytes(Dm, 1);
-    if (cx->geo_one_total + bytes > kAll) return false;
-    void* d = build_geo(cx->tab.primes + k, Dm, 1, st);
-    if (!d) return false;
-    cx->geo_one_total += bytes;
-    it = cx->geo_one.emplace(std::make_pair(k, Dm), d).first;
-  }
-  set_geo(it->second, Dm, 1, tab);
+bool geo_tables_of_prime(Context* cx, int D, int k, hipStream_t st, TablesDev* tab, TableRefs* refs) {
+  TableRefs gone;
+  const auto t = cx->geo_one.get(k, (D + 255) & ~255, 1, true, geo_table_bytes,
+                                 [&](int Dm, int) { return build_geo(cx->tab.primes + k, Dm, 1, st); }, &gone);
+  if (!t.mem) return false;
+  refs->push_back(t.mem);
+  set_geo(t.mem->p, t.a, 1, tab);
   return true;
 }
 
-void pow_planes_device(Context* cx, int D, int P, hipStream_t st, TablesDev* tab) {
-  constexpr size_t kOne = (size_t)32 << 20, kAll = (size_t)256 << 20;
-  std::lock_guard<std::mutex> lk(cx->pow_mu);
+void pow_planes_device(Context* cx, int D, int P, hipStream_t st, TablesDev* tab, TableRefs* refs) {
+  // (on the geometric nodes no larger than asked: tab's node tables end there)
   const bool geo = tab->qpow != nullptr;
-  int nb = (D + 255) / 256 * 4, Pm = std::min((P + 31) & ~31, cx->tab.K);
-  const Context::PowTable* hit = nullptr;
-  size_t total = 0;
-  for (const auto& t : cx->pow) {
-    total += t.bytes;
-    if (t.geo == geo && t.nb >= nb && t.P >= P && (!hit || t.bytes < hit->bytes)) hit = &t;
-  }
-  if (!hit) {
-    // large enough for the earlier calls too, if the nodes' tables and the limits allow
-    int nb1 = nb, P1 = Pm;
-    for (const auto& t : cx->pow)
-      if (t.geo == geo) nb1 = std::max(nb1, t.nb), P1 = std::max(P1, t.P);
-    if (!geo && pow_planes_bytes(nb1, P1) <= kOne && total + pow_planes_bytes(nb1, P1) <= kAll) nb = nb1, Pm = P1;
-    const size_t bytes = pow_planes_bytes(nb, Pm);
-    if (bytes > kOne || total + bytes > kAll) return;
-    int8_t* d = nullptr;
-    if (hipMalloc((void**)&d, bytes) != hipSuccess) {
-      (void)hipGetLastError();
-      return;
-    }
-    launch_pow_planes(*tab, nb, Pm, d, st);
-    if (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess) {
-      (void)hipFree(d);
-      return;
-    }
-    cx->pow.push_back({d, geo, nb, Pm, bytes});
-    hit = &cx->pow.back();
-  }
-  tab->pow_planes = hit->p;
-  tab->pow_nb = hit->nb;
+  TableRefs gone;
+  const auto t = cx->pow.get(geo, (D + 255) / 256 * 4, std::min((P + 31) & ~31, cx->tab.K), !geo, pow_planes_bytes,
+                             [&](int nb, int Pm) {
+                               return build_table(pow_planes_bytes(nb, Pm), st, [&](void* d) {
+                                 launch_pow_planes(*tab, nb, Pm, (int8_t*)d, st);
+                               });
+                             },
+                             &gone);
+  graph_forget(cx, gone);
+  if (!t.mem) return;
+  refs->push_back(t.mem);
+  tab->pow_planes = (const int8_t*)t.mem->p;
+  tab->pow_nb = t.a;
 }
 
 const int8_t* vinv_device(Context* cx, int D, int P, hipStream_t st) {

@@ -4,15 +4,18 @@
 #include <stdint.h>
 
 #include <atomic>
+#include <functional>
 #include <map>
 #include <memory>
 #include <mutex>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/bires.h"
 #include "job.hpp"
 #include "plan.hpp"
+#include "table_cache.hpp"
 
 namespace bires {
 
@@ -21,6 +24,8 @@ namespace bires {
 class Pool {
  public:
   explicit Pool(bool pinned) : pinned_(pinned) {}
+  // called when an allocation fails, before it is tried again
+  void set_on_full(std::function<void()> f) { on_full_ = std::move(f); }
   void* alloc(size_t bytes);
   void release(void* p);
   size_t cached_bytes();
@@ -32,6 +37,7 @@ class Pool {
     size_t bytes;
   };
   bool pinned_;
+  std::function<void()> on_full_;
   std::mutex mu_;
   std::vector<Block> free_;
   std::vector<Block> used_;
@@ -58,6 +64,23 @@ struct DevImage {
   ~DevImage() {
     if (d) (void)hipFree(d);
   }
+};
+// A table in device memory (TableCache); freed with its last holder.
+struct DevTable {
+  void* p = nullptr;
+  DevTable() = default;
+  DevTable(const DevTable&) = delete;
+  DevTable& operator=(const DevTable&) = delete;
+  ~DevTable() {
+    if (p) (void)hipFree(p);
+  }
+};
+using TableRef = std::shared_ptr<DevTable>;
+using TableRefs = std::vector<TableRef>;  // the tables that a call's launches, or a graph's, read
+// A captured launch sequence with the tables that its launches read.
+struct CachedGraph {
+  hipGraphExec_t exec = nullptr;
+  TableRefs tables;
 };
 struct SpecCache {
   std::mutex mu;
@@ -93,16 +116,15 @@ struct Context {
   int64_t kernel_launches = 0;
   double host_us[BIRES_HOST_PHASES] = {0};
   int64_t host_calls = 0;
-  std::mutex crt_mu;
-  size_t crt_total = 0;                                 // bytes of the CRT tables above CRT_SMALL_PRIMES
-  std::map<int, const uint32_t*> crt;                   // P -> device table
+  // explicit CRT tables by prime count: up to CRT_SMALL_PRIMES (14 MiB at most), above
+  TableCache<DevTable> crt_small{(size_t)64 << 20, (size_t)64 << 20}, crt_big{(size_t)64 << 20, (size_t)1 << 30};
   std::atomic<int> eval_mode{BIRES_EVAL_AUTO};           // evaluation + elimination kernel (BIRES_EVAL_*)
   std::atomic<long long> schur_instances{0}, schur_fallbacks{0};  // Schur kernel statistics
   std::atomic<bool> graphs{false};                       // replay device sequences as captured graphs
   std::atomic<bool> plan_cache{true};                    // speculative reuse of the last call's plans
   SpecCache spec;
   std::mutex graph_mu;
-  std::map<uint64_t, hipGraphExec_t> graph_cache;       // sequence hash -> instantiated graph
+  std::map<uint64_t, CachedGraph> graph_cache;          // sequence hash -> instantiated graph
   std::vector<uint64_t> graph_order;                    // insertion order (oldest first)
   int64_t graph_captures = 0, graph_replays = 0;        // under graph_mu
   std::mutex itab_mu;                                   // interpolation block tables (interp_tables_device)
@@ -110,23 +132,10 @@ struct Context {
   int itab_nb = 0, itab_P = 0;
   size_t itab_qoff = 0;
   std::vector<uint32_t*> itab_retired;                  // outgrown tables (kernels in flight may still read them)
-  struct GeoTable {
-    void* p;
-    int D, P;
-    size_t bytes;
-  };
-  std::mutex geo_mu;                                    // tables of the geometric nodes (geo_tables_device)
-  std::vector<GeoTable> geo;
-  std::map<std::pair<int, int>, void*> geo_one;         // (prime, indices) -> the same of one prime
-  size_t geo_one_total = 0;                             // under geo_mu
-  struct PowTable {
-    const int8_t* p;
-    bool geo;
-    int nb, P;
-    size_t bytes;
-  };
-  std::mutex pow_mu;                                    // powers of the points (pow_planes_device)
-  std::vector<PowTable> pow;
+  // geometric nodes (sizes: indices, primes): the batches' tables; by prime, one prime's (psc.cpp)
+  TableCache<DevTable> geo{(size_t)512 << 20, (size_t)1 << 30}, geo_one{(size_t)1 << 20, (size_t)64 << 20};
+  // powers of the points (tag: geometric nodes or 0, 1, ..; sizes: blocks of 64 points, primes)
+  TableCache<DevTable> pow{(size_t)32 << 20, (size_t)256 << 20};
   std::mutex ev_mu;
   std::vector<hipEvent_t> ev_free;                      // completion events of batched calls, reused
   std::mutex vinv_mu;
@@ -146,10 +155,11 @@ int scratch_address(uint8_t** ptr, size_t* bytes);
 
 // Captured device sequences keyed by the hash of their call arguments:
 // graph_launch launches a cached one (false if absent or the launch failed);
-// graph_store_launch caches a new executable (at most 32, the oldest is
-// destroyed after a device synchronisation) and launches it.
+// graph_store_launch caches a new executable with the tables that its launches
+// read (at most 32, the oldest is destroyed after a device synchronisation)
+// and launches it.
 bool graph_launch(Context* cx, uint64_t key, hipStream_t st);
-bool graph_store_launch(Context* cx, uint64_t key, hipGraphExec_t exec, hipStream_t st);
+bool graph_store_launch(Context* cx, uint64_t key, hipGraphExec_t exec, const TableRefs& tables, hipStream_t st);
 
 // Inverse Vandermonde digit planes for nodes 0..D-1 and the first P primes,
 // built on first use (on stream st, which is then synchronised) and kept;
@@ -162,27 +172,31 @@ const int8_t* vinv_device(Context* cx, int D, int P, hipStream_t st);
 bool interp_tables_device(Context* cx, int blocks, int primes, hipStream_t st, const uint32_t** W,
                           const uint32_t** Q, int* nb);
 
+// The tables below are built on first use (on `st`, which is then synchronised)
+// and kept for later calls within the limits of their TableCache, or until an
+// allocation of the device pool fails.  *refs receives a reference to each
+// table that a function hands out; the caller keeps it until its launches have
+// ended.
+
 // Fills *tab's tables of the geometric nodes for at least D points and P primes
-// (built on `st`, which is then synchronised, and kept: at most 512 MiB each
-// and 1 GiB in all; never freed, calls in flight may read them).  False when
-// they would not fit or the build failed: the call then uses the nodes 0..D-1.
-bool geo_tables_device(Context* cx, int D, int P, hipStream_t st, TablesDev* tab);
+// (at most 512 MiB each, 1 GiB in all).  False when they would be larger or the
+// build failed: the call then uses the nodes 0..D-1.
+bool geo_tables_device(Context* cx, int D, int P, hipStream_t st, TablesDev* tab, TableRefs* refs);
 // The same for table prime k alone, as prime 0 of *tab (the tables shifted to
 // it): at most 622 KB, kept apart from the batches' tables, 64 MiB in all.
-bool geo_tables_of_prime(Context* cx, int D, int k, hipStream_t st, TablesDev* tab);
+bool geo_tables_of_prime(Context* cx, int D, int k, hipStream_t st, TablesDev* tab, TableRefs* refs);
 // Fills tab->pow_planes for at least D points and P primes on the nodes tab is set
-// up for; leaves it null when the table would exceed its limits (32 MiB, 256 MiB
-// for all).
-void pow_planes_device(Context* cx, int D, int P, hipStream_t st, TablesDev* tab);
+// up for; leaves it null when the table would be larger than 32 MiB (256 MiB
+// for all) or the build failed.
+void pow_planes_device(Context* cx, int D, int P, hipStream_t st, TablesDev* tab, TableRefs* refs);
 
-// The explicit CRT's tables of P primes (limbs of the modulus: radix_limbs),
-// built on first use (on stream st, which is then synchronised) and kept;
-// nullptr on failure, or when those of the counts above CRT_SMALL_PRIMES would
-// exceed 1 GiB in all (the others take 14 MiB at most).  A caller asks only
-// for counts whose launch fits (crt_fits).
-const uint32_t* crt_device(Context* cx, int P, hipStream_t st);
+// The explicit CRT's tables of P primes (limbs of the modulus: radix_limbs);
+// nullptr on failure.  Those of the counts up to CRT_SMALL_PRIMES stay (14 MiB at
+// most), the others within 1 GiB.  A caller asks only for counts whose launch
+// fits (crt_fits).
+const uint32_t* crt_device(Context* cx, int P, hipStream_t st, TableRefs* refs);
 // The same when it already exists, else nullptr (never allocates).
-const uint32_t* crt_device_cached(Context* cx, int P);
+const uint32_t* crt_device_cached(Context* cx, int P, TableRefs* refs);
 
 // Autotuning key of a planned batch: log2-buckets of the total (prime, point)
 // instances, of the largest m + n and of the largest prime count.

@@ -255,9 +255,10 @@ int reconstruct(Context* cx, const std::vector<int>& S, const std::vector<const 
   const int nj = (int)src.size(), P = (int)S.size();  // P >= 1
   const int cls = crt_class(P), LM = cls >= 0 ? radix_limbs(P) : 0;
   const size_t lds = cls < 0 ? 0 : cls == CRT_BIG ? crt_big_lds_bytes(P, LM) : crt_lds_bytes(LM + 1, P);
+  TableRefs tables;  // (every return below follows the stream's work, or a device error)
   const uint32_t* ct = nullptr;
   if (S.back() == P - 1 && crt_fits(P, LM, LM + 1, cx->lds_per_block) && lds <= cx->lds_per_block)
-    ct = crt_device(cx, P, st);
+    ct = crt_device(cx, P, st, &tables);
   const int Lcap = ct ? LM + 1 : P + 1, Lacc = ct ? 0 : P + 1;
   const int rows = !ct ? 1 : cls == CRT_BIG ? 32 : crt_rows_per_block(P);
   std::vector<ModP> primes;

@@ -96,6 +96,7 @@ struct PscRun {
     }
   };
   DevBuf ws, host;
+  TableRefs tables;
   const uint32_t* coefs = nullptr;
   int K = 0, D = 0, m = -1, n = -1;
   Queued queued;  // (the last member: waits before the buffers go)
@@ -187,7 +188,7 @@ static int psc_device(Context* cx, const HostJob& h, int kind, int kp, int kmax,
   }
   is[K] = K;
   TablesDev tab = shifted(cx->tab, kp);
-  const bool geo = geo_tables_of_prime(cx, D, kp, st, &tab);
+  const bool geo = geo_tables_of_prime(cx, D, kp, st, &tab, &r.tables);
   r.queued.st = st;
   r.queued.on = true;
   DEV(hipMemcpyAsync(r.ws.p, H, up_end, hipMemcpyHostToDevice, st));

@@ -1,7 +1,8 @@
 """Graph replay and the tables that launches take by value: two batches alike in
 every block count, size and offset, whose degree-20 pairs need 256 and 256
 primes in one and 192 and 320 in the other, so that only the stored powers of
-the points differ between their launch sequences."""
+the points differ between their launch sequences; and point counts that grow
+from call to call, each with tables that take the place of the former ones."""
 
 import functools
 
@@ -52,3 +53,28 @@ def test_a_replayed_graph_reads_its_own_tables(order, monkeypatch):
         want.append(b.results())
     for i, r in got:
         assert r == want[i]
+
+
+def test_outgrown_tables_and_their_graphs():
+    # 16 sizes up to 7936 points, each replayed, then all again on the last tables
+    batches = [br.DeviceBatch([("res",) + synth.random_rect(71 + k, 1, 5, 1, 256 + 512 * k - 6, 40) + ("y",)])
+               for k in range(16)]
+    br.set_plan_cache(False)
+    try:
+        br.set_graphs(True)
+        got = []
+        for b in [b for b in batches for _ in range(3)] + batches:
+            for t in b.out_tensors:
+                t.fill_(-1)
+            b.run()
+            got.append(b.results())
+    finally:
+        br.set_graphs(False)
+        br.set_plan_cache(True)
+    try:
+        br.set_eval_kernel("lds")
+        for i, b in enumerate(batches):
+            b.run()
+            assert got[3 * i:3 * i + 3] + [got[48 + i]] == [b.results()] * 4
+    finally:
+        br.set_eval_kernel("auto")
