@@ -493,12 +493,12 @@ __device__ __forceinline__ void ee_first(int32_t (&X)[C], int32_t (&Y)[C], int a
 // a0: A's balanced leading coefficient.  post(bs, l2, lead) is called after
 // every step with the divisor's degree and the remainder's leading coefficient.
 // Returns false (on every lane) when a divisor's leading coefficient vanishes at
-// some lane's point.
+// the point of one of the lanes `live`.
 #define EE_CHAIN_STEP(BV)                                                  \
   if constexpr (BV <= CH && BV + 1 < C) {                                  \
     if (bs >= BV) {                                                        \
       const int32_t lb = balance(((BV) & 1) ? X[0] : Y[0], q.p);           \
-      if (__ballot(lb == 0) != 0ull) return false;                         \
+      if ((__ballot(lb == 0) & live) != 0ull) return false;                \
       const int32_t l2 = ee_step<C, BV, ((BV) & 1) == 0>(X, Y, a0, lb, q); \
       a0 = lb;                                                             \
       post(BV, l2, ((BV) & 1) ? Y[0] : X[0]);                              \
@@ -507,14 +507,14 @@ __device__ __forceinline__ void ee_first(int32_t (&X)[C], int32_t (&Y)[C], int a
 #define EE_ANY_STEP(AX)                                             \
   {                                                                 \
     const int32_t lb = balance(AX ? Y[0] : X[0], q.p);              \
-    if (__ballot(lb == 0) != 0ull) return false;                    \
+    if ((__ballot(lb == 0) & live) != 0ull) return false;           \
     const int32_t l2 = ee_step_any<C, CH, AX>(X, Y, bs, a0, lb, q); \
     a0 = lb;                                                        \
     post(bs, l2, AX ? X[0] : Y[0]);                                 \
     bs -= 1;                                                        \
   }
 template <int C, int CH, class F>
-__device__ __forceinline__ bool ee_chain(int32_t (&X)[C], int32_t (&Y)[C], int bs, int32_t a0, const SModP& q, F post) {
+__device__ __forceinline__ bool ee_chain(int32_t (&X)[C], int32_t (&Y)[C], int bs, int32_t a0, uint64_t live, const SModP& q, F post) {
   if constexpr (C > CH) {
     // pairs of an even and an odd step; an odd start skips the first even one
     // (conditional updates in place, not the two arms of a branch that merge)
@@ -645,6 +645,12 @@ __device__ __forceinline__ void ee_eval(const JobDev& J, int k, int blk, TablesD
   }
 }
 
+// The lanes of block blk that hold one of the D points.  The others, in the last
+// block, compute something of no consequence (with stored powers the powers of
+// the next nodes, but a^KW of point D - 1) and must not send the block to the
+// general kernel.
+__device__ __forceinline__ uint64_t live_lanes(int D, int blk) { return ~0ull >> (64 - min(64, D - 64 * blk)); }
+
 // Returns false (on every lane) when the block must be recomputed by
 // dev_eval_elim: a leading coefficient vanishes at some lane's point, or a
 // remainder is shorter than a normal sequence's.  Needs 1 <= m, n < C.
@@ -662,6 +668,7 @@ __device__ __forceinline__ bool dev_ee(const JobDev& J, int lb_, TablesDev tab, 
   const bool normal = as0 == bs0 + 1;
   const bool ax = normal ? (bs0 & 1) == 0 : ((bs0 - 1) & 1) != 0;
   const bool xf = ax != sw;  // X holds f
+  const uint64_t live = live_lanes(J.D, blk);
   EvalCtx E;
   int32_t X[C], Y[C];
   ee_eval<C, KW>(J, k, blk, tab, planes, xf, E, X, Y, q);
@@ -671,7 +678,7 @@ __device__ __forceinline__ bool dev_ee(const JobDev& J, int lb_, TablesDev tab, 
   int32_t a0 = balance(sel(ax, X[0], Y[0]), q.p);
   {
     const int32_t b0 = balance(sel(ax, Y[0], X[0]), q.p);
-    if (__ballot(a0 == 0 || b0 == 0) != 0ull) return false;
+    if ((__ballot(a0 == 0 || b0 == 0) & live) != 0ull) return false;
     if (!normal) {
       int fx = ax, fy = !ax;
       asm("" : "+s"(fx), "+s"(fy));
@@ -693,14 +700,14 @@ __device__ __forceinline__ bool dev_ee(const JobDev& J, int lb_, TablesDev tab, 
       bs -= 1;
     }
   }
-  if (!ee_chain<C, CH>(X, Y, bs, a0, q, [&](int b, int32_t l2, int32_t) __attribute__((always_inline)) {
+  if (!ee_chain<C, CH>(X, Y, bs, a0, live, q, [&](int b, int32_t l2, int32_t) __attribute__((always_inline)) {
         pfx = smul(pfx, l2, q);
         if (b > 1) den = smul(den, pfx, q);
       }))
     return false;
   // the constant remainder: degree 0 is even, so A (degree 1) is X and it is in Y
   const int32_t last = balance(Y[0], q.p);
-  if (__ballot(last == 0) != 0ull) return false;
+  if ((__ballot(last == 0) & live) != 0ull) return false;
   num = smul(num, last, q);
   int32_t r = smul(num, spow(balance(den, q.p), q.p - 2u, q), q);
   if (neg) r = -r;
@@ -786,12 +793,13 @@ __device__ __forceinline__ bool dev_psc(const JobDev& J, int blk, TablesDev tab,
   const bool sw = m < n, eq = m == n;
   const int bs0 = sw ? m : n;
   const bool ax = eq ? ((bs0 - 1) & 1) != 0 : (bs0 & 1) == 0;
+  const uint64_t live = live_lanes(J.D, blk);
   EvalCtx E;
   int32_t X[C], Y[C];
   ee_eval<C, KW>(J, 0, blk, tab, planes, ax != sw, E, X, Y, q);
   int32_t a0 = balance(sel(ax, X[0], Y[0]), q.p);
   const int32_t b0 = balance(sel(ax, Y[0], X[0]), q.p);
-  if (__ballot(a0 == 0 || b0 == 0) != 0ull) return false;
+  if ((__ballot(a0 == 0 || b0 == 0) & live) != 0ull) return false;
   int E0 = sw ? (m * n) & 1 : 0, E1 = sw ? (m + n + 1) & 1 : 0;
   int32_t Nn = E.one, Nd = E.one, sA = E.one, sB = E.one;
   auto emit = [&](int i, int32_t vn, int32_t vd) __attribute__((always_inline)) {
@@ -817,7 +825,7 @@ __device__ __forceinline__ bool dev_psc(const JobDev& J, int blk, TablesDev tab,
     nm[bs0 * 64 + l] = b0;  // lc(B)^(a - b)
     dn[bs0 * 64 + l] = E.one;
   }
-  if (!ee_chain<C, CH>(X, Y, bs, a0, q, [&](int b, int32_t l2, int32_t lead) __attribute__((always_inline)) {
+  if (!ee_chain<C, CH>(X, Y, bs, a0, live, q, [&](int b, int32_t l2, int32_t lead) __attribute__((always_inline)) {
         Nn = smul(Nn, l2, q);
         Nd = smul(smul(Nd, sB, q), sB, q);
         const int32_t sR = smul(l2, sA, q);
