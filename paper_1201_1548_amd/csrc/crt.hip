@@ -105,7 +105,7 @@ void launch_crt_tables(TablesDev tab, int P, int LM, uint32_t* buf, hipStream_t 
 //      tile through LDS, and lane x + 32 h folds row x's 16 byte columns of
 //      half h into four limbs of X - t M with carry 0 coming in.  Limbs go to the
 //      output row; the carry out of each four-limb segment, its lowest limb
-//      and whether the other three are all zeros or all ones go to LDS.
+//      and whether the other three are all zeros go to LDS.
 //   3. One lane per row adds each segment's carry into the next one's lowest
 //      limb; a carry that leaves that limb (about one in 2^12) ripples through
 //      the other three.
@@ -245,8 +245,7 @@ __global__ __launch_bounds__(64 * CBW) void k_crt_big(const JobDev* jobs, const 
       }
       cr[row * ld + seg] = (int32_t)carry;  // |S_c| 2^24 / 2^32 and t M's share: below 2^27
       l0[row * ld + seg] = limb[0];
-      fl[row * ld + seg] = (uint8_t)(((limb[1] | limb[2] | limb[3]) == 0u ? 1 : 0) |
-                                     ((limb[1] & limb[2] & limb[3]) == 0xFFFFFFFFu ? 2 : 0));
+      fl[row * ld + seg] = (limb[1] | limb[2] | limb[3]) == 0u;
       group_sync<true>();
     }
   }
@@ -269,7 +268,7 @@ __global__ __launch_bounds__(64 * CBW) void k_crt_big(const JobDev* jobs, const 
       int64_t up = v >> 32;
       if (nl != low) put(4 * s, nl);
       if (up == 0) {
-        nz |= nl != 0u || !(fl[row * ld + s] & 1);
+        nz |= nl != 0u || !fl[row * ld + s];
       } else {
         nz |= nl != 0u;
         for (int w = 1; w < 4; ++w) {
