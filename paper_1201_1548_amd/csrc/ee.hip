@@ -893,7 +893,13 @@ void launch_eval_elim_rg(int C, const JobDev* jobs, const int* starts, int nj, i
     default: BIRES_EE_LAUNCH(68); break;
   }
 #undef BIRES_EE_LAUNCH
-  launch_eval_elim_fb(jobs, starts, nj, nblocks, max_words, fb_count, fb_queue, tab, s);
+  // One block per CU costs an empty queue next to nothing.  At capacity 68 as many as
+  // fit beside each other (34 KB of LDS each): a sequence that is not normal
+  // queues every block, and the general kernel would have had them all at once
+  // (20 pairs of degrees 64 and 62 in y, even: 36.6 ms with 256 blocks, 12.1
+  // with 1024, 10.9 by the general kernel alone).
+  const int fb_blocks = C == 68 ? 1024 : 256;
+  launch_eval_elim_fb(jobs, starts, nj, nblocks, fb_blocks, max_words, fb_count, fb_queue, tab, s);
 }
 
 }  // namespace bires

@@ -2697,10 +2697,10 @@ void launch_eval_elim(const JobDev* jobs, const int* starts, int nj, int nblocks
                      starts, nj, tab);
 }
 
-void launch_eval_elim_fb(const JobDev* jobs, const int* starts, int nj, int nblocks, int max_words,
+void launch_eval_elim_fb(const JobDev* jobs, const int* starts, int nj, int nblocks, int max_blocks, int max_words,
                          const int* fb_count, const int* fb_queue, TablesDev tab, hipStream_t s) {
-  hipLaunchKernelGGL(k_eval_elim_fb, dim3(std::min(nblocks, 256)), dim3(64), eval_elim_lds_bytes(max_words, 0), s,
-                     jobs, starts, nj, tab, fb_count, fb_queue);
+  hipLaunchKernelGGL(k_eval_elim_fb, dim3(std::min(nblocks, max_blocks)), dim3(64), eval_elim_lds_bytes(max_words, 0),
+                     s, jobs, starts, nj, tab, fb_count, fb_queue);
 }
 
 int schur_rows_per_lane(int m, int n) {

@@ -1,0 +1,42 @@
+"""Evaluation times of the registers' route against the general kernel's where the
+former has least to offer: it may lose what its attempt costs, no more."""
+
+import pytest
+
+import paper_1201_1548_amd as br
+from paper_1201_1548_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def evaluation_time(b, kernel):
+    """Milliseconds of the evaluation and elimination launches, best of five calls."""
+    try:
+        br.set_eval_kernel(kernel)
+        b.run()
+        b.run()
+        best = 1e30
+        for _ in range(5):
+            br.set_timing(True)
+            b.run()
+            ms, launches = br.kernel_time()
+            br.set_timing(False)
+            best = min(best, ms / launches)
+        return best, b.results()
+    finally:
+        br.set_timing(False)
+        br.set_eval_kernel("auto")
+
+
+@pytest.mark.parametrize("m,n", [(64, 62), (66, 64)])
+def test_sequences_that_are_not_normal(m, n):
+    # even in y: every remainder skips a degree, every block is recomputed
+    F, G = synth.random_rect(2, m, 10, n, 10, 30)
+    F, G = ([r if j % 2 == 0 else [0] * len(r) for j, r in enumerate(P)] for P in (F, G))
+    b = br.DeviceBatch([("res", F, G, "y")] * 20)
+    general, want = evaluation_time(b, "lds")
+    registers, got = evaluation_time(b, "auto")
+    assert got == want
+    # the attempt is one evaluation and a step of a chain: a tenth measured, 3.3 times
+    # with a quarter of the blocks that the general kernel has at once
+    assert registers < 1.5 * general
