@@ -179,6 +179,7 @@ __device__ void dev_reduce(const JobDev& J, int lb, int k0, int k1, TablesDev ta
   const int ld = isg ? J.ldg : J.ldf;
   const int j = t / lp, i = t - j * lp;
   uint32_t* dst = (isg ? J.res_g : J.res_f) + t;
+  const bool dig = J.dig != 0;  // (before the stores, which could change it as far as the compiler knows)
   k1 = min(J.P, k1);
   if (i >= ld) {
     for (int k = k0; k < k1; ++k) dst[(size_t)k * T] = 0u;
@@ -224,7 +225,7 @@ __device__ void dev_reduce(const JobDev& J, int lb, int k0, int k1, TablesDev ta
         uint32_t x = mmul(w0, q.r2, q);
         if (neg) x = msub(x, q.r2, q.p);
         if (mult) x = mmul(x, to_mont(mult, q), q);
-        dst[(size_t)(kb + j) * T] = J.dig ? digits4(x, q.p) : x;
+        dst[(size_t)(kb + j) * T] = dig ? digits4(x, q.p) : x;
       }
     }
     return;
@@ -269,7 +270,7 @@ __device__ void dev_reduce(const JobDev& J, int lb, int k0, int k1, TablesDev ta
       uint32_t x = fold96(A, q[j]);
       if (negv) x = msub(x, from_mont(c[j], q[j]), q[j].p);  // c = 2^{32 L} R^2
       if (mult) x = mmul(x, to_mont(mult, q[j]), q[j]);
-      dst[(size_t)(kb + j) * T] = J.dig ? digits4(x, q[j].p) : x;
+      dst[(size_t)(kb + j) * T] = dig ? digits4(x, q[j].p) : x;
     }
   }
 }
