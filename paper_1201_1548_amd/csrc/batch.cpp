@@ -468,8 +468,18 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
   int rw[NRG] = {0};
   int sw[NSC] = {0};
   int gmax[GEO_CLASSES] = {0};  // interpolation on the geometric nodes: largest D of each class
+  // (a class without blocks has no array and no map on the device: for a batch of
+  // many small jobs a map costs what a kernel does)
   std::vector<int> starts[NK];
-  for (auto& v : starts) v.assign(nj + 1, 0);
+  auto put = [&](int kk, int i, int blocks) {
+    if (starts[kk].empty()) starts[kk].assign(nj + 1, 0);
+    starts[kk][i + 1] = blocks;
+  };
+  auto sum_up = [&](int kk) {
+    for (size_t i = 1; i < starts[kk].size(); ++i) starts[kk][i] += starts[kk][i - 1];
+  };
+  auto nb_of = [&](int kk) { return starts[kk].empty() ? 0 : starts[kk][nj]; };
+  auto has_blocks = [&](int kk, int i) { return !starts[kk].empty() && starts[kk][i + 1] != starts[kk][i]; };
   // the schedule: from the autotuner's table for the batch's size key
   long long instances = 0;
   int max_r = 0, keyP = 1;
@@ -508,28 +518,25 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
     }
     maxP = std::max(maxP, p.P);
     maxD = std::max(maxD, p.D);
-    starts[K_RED][i + 1] = (x.Tf + 63) / 64 + (x.Tg + 63) / 64;
+    put(K_RED, i, (x.Tf + 63) / 64 + (x.Tg + 63) / 64);
     const int nr = schur ? schur_rows_per_lane(p.m, p.n) : 0;
     const int rc = cx->eval_mode == BIRES_EVAL_AUTO ? eval_elim_rg_capacity(p.m, p.n) : 0;
     if (nr) {
-      starts[K_SC0 + nr - 1][i + 1] = p.P * p.D;
+      put(K_SC0 + nr - 1, i, p.P * p.D);
       sw[nr - 1] = std::max(sw[nr - 1], p.m + p.n + 2);
     } else if (rc) {
       int r = 0;
       while (rg_cap[r] != rc) ++r;
       x.dig = sched != BIRES_SCHEDULE_FUSED;  // (the persistent launch reads plain residues)
-      starts[K_RG0 + r][i + 1] = p.P * ((p.D + 63) / 64);
+      put(K_RG0 + r, i, p.P * ((p.D + 63) / 64));
       rw[r] = std::max(rw[r], p.m + p.n + 2);
     } else {
       int bk = 0;
       while (p.m + p.n + 2 > bucket_words[bk]) ++bk;
-      starts[K_EE0 + bk][i + 1] = p.P * ((p.D + 63) / 64);
+      put(K_EE0 + bk, i, p.P * ((p.D + 63) / 64));
       bw[bk] = std::max(bw[bk], p.m + p.n + 2);
       br_[bk] = std::max(br_[bk], x.Tf + x.Tg);
     }
-    starts[K_IP][i + 1] = p.P;
-    starts[K_GE0 + geo_class(p.D)][i + 1] = p.P;
-    gmax[geo_class(p.D)] = std::max(gmax[geo_class(p.D)], p.D);
   }
   int maxLcap = 1;
   for (int i = 0; i < nj; ++i)
@@ -599,17 +606,16 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
       const int c = cls[i];
       if (!fused && c >= 0 && crt_lds[c] <= cx->lds_per_block) {
         const int r = c == CRT_BIG ? 32 : crt_rows_per_block(crtP[c]);
-        starts[K_CRT0 + c][i + 1] = (rows + r - 1) / r;
+        put(K_CRT0 + c, i, (rows + r - 1) / r);
       } else if (!use_crt) {
-        starts[K_MRC][i + 1] = x.pl.D;  // Garner: one wave per coefficient
-        starts[K_SUM][i + 1] = (x.pl.D * x.Lacc + 255) / 256;
-        starts[K_CAR][i + 1] = (x.degcap + 1 + 63) / 64;
+        put(K_MRC, i, x.pl.D);  // Garner: one wave per coefficient
+        put(K_SUM, i, (x.pl.D * x.Lacc + 255) / 256);
+        put(K_CAR, i, (x.degcap + 1 + 63) / 64);
       }
     }
   }
-  for (auto& v : starts)
-    for (int i = 0; i < nj; ++i) v[i + 1] += v[i];
-  if (!fused && !debug) P->schur_instances = (long long)starts[K_SC0][nj] + starts[K_SC0 + 1][nj];
+  for (int kk = 0; kk < NK; ++kk) sum_up(kk);
+  if (!fused && !debug) P->schur_instances = (long long)nb_of(K_SC0) + nb_of(K_SC0 + 1);
   // interpolation on the matrix cores when at least 32 jobs share D and P
   // (all active jobs of the batch)
   std::vector<int> group;
@@ -644,12 +650,21 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
     itW = itQ = nullptr;
     itNB = 0;
   }
+  // blocks of the interpolation: one per job and prime
+  for (int i = 0; i < nj && group.empty() && !debug; ++i) {
+    if (w[i].status || !w[i].active) continue;
+    const int D = w[i].pl.D, c = geo_class(D);
+    put(geo ? K_GE0 + c : K_IP, i, w[i].pl.P);
+    if (geo) gmax[c] = std::max(gmax[c], D);
+  }
+  sum_up(K_IP);
+  for (int c = 0; c < GEO_CLASSES; ++c) sum_up(K_GE0 + c);
   // the powers of the points, for launches that fill the chip: below two blocks
   // per SIMD the evaluation computes them in the time that they take to arrive
-  if (!debug && !noalloc && !fused && !schur && starts[K_RG0][nj] + starts[K_RG0 + 1][nj] >= 2048) {
+  if (!debug && !noalloc && !fused && !schur && nb_of(K_RG0) + nb_of(K_RG0 + 1) >= 2048) {
     int rD = 0, rP = 0;
     for (int i = 0; i < nj; ++i)
-      if (starts[K_RG0][i + 1] != starts[K_RG0][i] || starts[K_RG0 + 1][i + 1] != starts[K_RG0 + 1][i])
+      if (has_blocks(K_RG0, i) || has_blocks(K_RG0 + 1, i))
         rD = std::max(rD, w[i].pl.D), rP = std::max(rP, w[i].pl.P);
     pow_planes_device(cx, rD, rP, st, &etab, &by_value);
   }
@@ -690,7 +705,7 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
   }
   const size_t o_ffbq = ws.take(sizeof(int) * (fused ? (size_t)fst_rg[nj] : 0));
   size_t o_fbq[NRG];  // queues of blocks recomputed by the LDS kernel
-  for (int r = 0; r < NRG; ++r) o_fbq[r] = ws.take(sizeof(int) * (size_t)starts[K_RG0 + r][nj]);
+  for (int r = 0; r < NRG; ++r) o_fbq[r] = ws.take(sizeof(int) * (size_t)nb_of(K_RG0 + r));
   // results for host memory: one region, one copy back
   const size_t o_outs = ws.take(noalloc ? 0 : hout.bytes);
   if (!noalloc)
@@ -705,7 +720,10 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
   const size_t o_fbc = ws.take(sizeof(int) * NRG);                         // queue lengths, uploaded as zero
   for (int i = 0; i < nj; ++i)
     if (!w[i].status && w[i].active) w[i].o_rowdeg = ws.take((size_t)(w[i].pl.m + w[i].pl.n + 2) * 4);
-  const size_t o_maps = ws.take(sizeof(int) * (size_t)NK * (nj + 1));
+  int slot[NK] = {0}, maps = 0;
+  for (int kk = 0; kk < NK; ++kk)
+    if (!starts[kk].empty()) slot[kk] = maps++;
+  const size_t o_maps = ws.take(sizeof(int) * (size_t)maps * (nj + 1));
   // the group's coefs pointers
   const size_t o_gco = ws.take(sizeof(uint32_t*) * group.size());
   // the fused launch's block maps (register Euclid, LDS kernel, CRT) and its
@@ -719,7 +737,7 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
   if (noalloc) {
     // the workspace follows the input region in the scratch array
     const size_t base = (in.bytes + 255) & ~(size_t)255;
-    const size_t beside = sizeof(int) * (size_t)starts[K_RG0 + NRG - 1][nj] + 1024;
+    const size_t beside = sizeof(int) * (size_t)nb_of(K_RG0 + NRG - 1) + 1024;
     if (base + ws.bytes > cx->scratch_bytes + std::min(beside, NOALLOC_MARGIN)) return BIRES_ETOOBIG;
     D0 = cx->scratch + base;
     P->hv_meta.resize(meta_end - meta_begin);
@@ -791,8 +809,10 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
   }
   int* hm = (int*)(H0 + o_maps);
   const int* dm = (const int*)(D0 + o_maps);
-  for (int kk = 0; kk < NK; ++kk) std::memcpy(hm + (size_t)kk * (nj + 1), starts[kk].data(), sizeof(int) * (nj + 1));
-  auto st_of = [&](int kk) { return dm + (size_t)kk * (nj + 1); };
+  for (int kk = 0; kk < NK; ++kk)
+    if (!starts[kk].empty())
+      std::memcpy(hm + (size_t)slot[kk] * (nj + 1), starts[kk].data(), sizeof(int) * (nj + 1));
+  auto st_of = [&](int kk) { return dm + (size_t)slot[kk] * (nj + 1); };
   if (!group.empty()) {
     uint32_t** gco = (uint32_t**)(H0 + o_gco);
     for (size_t n = 0; n < group.size(); ++n) {
@@ -811,7 +831,6 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
     std::memcpy(H0 + o_fst + sizeof(int) * 2 * (nj + 1), fst_crt.data(), sizeof(int) * (nj + 1));
     std::memset(H0 + o_fctr, 0, sizeof(int) * F_CTR);
   }
-  auto nb_of = [&](int kk) { return starts[kk][nj]; };
   hc.mark(3);
   // special results of device-memory outputs are written on the stream
   // (outside any captured graph: memset nodes are not used in graphs)
