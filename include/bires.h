@@ -328,7 +328,8 @@ int bires_set_schedule(int schedule);
  *   BIRES_EVAL_AUTO (default): jobs with 1 <= min(m, n) and max(m, n) < 68
  *     (m, n: degrees in the eliminated variable) keep the coefficient arrays in
  *     registers; blocks that meet a vanishing leading coefficient or a
- *     degree drop are recomputed by the general kernel; other jobs use it;
+ *     degree drop are recomputed by the general kernel; other jobs use it,
+ *     and so do small ones that make up a call (degrees up to 8, short rows);
  *   BIRES_EVAL_LDS: every job uses the general kernel (both arrays in LDS);
  *   BIRES_EVAL_SCHUR: jobs with 1 <= min(m, n) and m + n <= 128 use the
  *     Schur kernel of BIRES_SCHEDULE_SCHUR (instances whose pivot vanishes mod

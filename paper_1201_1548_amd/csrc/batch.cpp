@@ -496,6 +496,14 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
   }
   const int sched = (debug || noalloc || instances == 0) ? BIRES_SCHEDULE_STAGED : schedule_for(cx, key);
   const bool schur = cx->eval_mode == BIRES_EVAL_SCHUR || sched == BIRES_SCHEDULE_SCHUR;
+  // Light jobs go to the general kernel when they are the larger part of what
+  // capacity 24 holds; fewer ride along with that capacity's launch, whose time
+  // they hardly add to.
+  auto light = [&](const Plan& p) { return eval_elim_light(p.m, p.n, std::max(p.dxf, p.dxg) + 1, instances); };
+  long long light_balance = 0;
+  for (int i = 0; i < nj; ++i)
+    if (!w[i].status && w[i].active && eval_elim_rg_capacity(w[i].pl.m, w[i].pl.n) == 24)
+      light_balance += (light(w[i].pl) ? 1 : -1) * (long long)w[i].pl.P * w[i].pl.D;
   int maxP = 1, maxD = 1;
   for (int i = 0; i < nj; ++i) {
     Work& x = w[i];
@@ -520,7 +528,8 @@ int launch_impl(Context* cx, const std::vector<JobIn>& jobs_in, int mem, hipStre
     maxD = std::max(maxD, p.D);
     put(K_RED, i, (x.Tf + 63) / 64 + (x.Tg + 63) / 64);
     const int nr = schur ? schur_rows_per_lane(p.m, p.n) : 0;
-    const int rc = cx->eval_mode == BIRES_EVAL_AUTO ? eval_elim_rg_capacity(p.m, p.n) : 0;
+    int rc = cx->eval_mode == BIRES_EVAL_AUTO ? eval_elim_rg_capacity(p.m, p.n) : 0;
+    if (rc == 24 && light_balance > 0 && light(p)) rc = 0;
     if (nr) {
       put(K_SC0 + nr - 1, i, p.P * p.D);
       sw[nr - 1] = std::max(sw[nr - 1], p.m + p.n + 2);

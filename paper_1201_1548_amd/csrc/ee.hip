@@ -882,6 +882,27 @@ int eval_elim_rg_capacity(int m, int n) {
   return d < 24 ? 24 : d < 32 ? 32 : d < 48 ? 48 : d < 68 ? 68 : 0;
 }
 
+// Jobs that the general kernel does faster than capacity 24, by degree d, row length
+// and the call's size: an instance costs it what d and the row (in pieces of 24
+// coefficients) ask for, while ee24 evaluates 16 rows at 64 points whatever they
+// are, a second time from 33 coefficients on, and has its recomputing launch
+// behind it.  Below a block per SIMD the latency of the two counts, ee24's being
+// the same for all d, above it the instructions.  Evaluation in us, general and
+// ee24 (m = n = d, coefficients of 20 to 40 bits):
+//   2000 pairs, rows of 4   d = 1 14, 28   d = 2 23, 39   d = 4 43, 60   d = 8 110, 129
+//                                          d = 10 172, 163
+//   300 pairs, rows of 21   d = 2 15, 18   d = 6 64, 66   d = 7 94, 89
+//   300 pairs, rows of 25   d = 3 28, 30   d = 4 46, 44
+//   300 pairs, rows of 33   d = 2 21, 37   d = 8 261, 279 d = 10 503, 434
+//   1 pair, rows of 4       d = 1 7.7, 14.3  d = 4 13.1, 15.3  d = 7 16.2, 15.7
+//   1 pair, rows of 12      d = 1 8.1, 14.3  d = 4 14.8, 15.2  d = 5 16.0, 15.5
+bool eval_elim_light(int m, int n, int row, long long instances) {
+  const int d = std::max(m, n);
+  if (d * (row + 8) <= 80) return true;
+  if (instances < 64 * 1024) return false;
+  return d <= (row <= 16 ? 8 : row <= 24 ? 6 : row <= 32 ? 3 : row <= 48 ? 8 : 5);
+}
+
 void launch_eval_elim_rg(int C, const JobDev* jobs, const int* starts, int nj, int nblocks, int max_words,
                          int* fb_count, int* fb_queue, TablesDev tab, hipStream_t s) {
 #define BIRES_EE_LAUNCH(N) \

@@ -53,6 +53,9 @@ void launch_eval_elim(const JobDev* jobs, const int* starts, int nj, int nblocks
 // workspace.
 constexpr size_t EE_SLACK_BYTES = 512;
 int eval_elim_rg_capacity(int m, int n);
+// Whether a job of capacity 24 is better left to the general kernel (row: the
+// coefficients of its longest row; instances: points times primes of the call).
+bool eval_elim_light(int m, int n, int row, long long instances);
 void launch_eval_elim_rg(int C, const JobDev* jobs, const int* starts, int nj, int nblocks, int max_words,
                          int* fb_count, int* fb_queue, TablesDev tab, hipStream_t s);
 // TablesDev::pow_planes for blocks < nb and primes < P on tab's nodes.

@@ -1,5 +1,5 @@
-"""Evaluation times of the registers' route against the general kernel's where the
-former has least to offer: it may lose what its attempt costs, no more."""
+"""Evaluation times of the default route against the general kernel's where the
+registers have least to offer: it may lose what their attempt costs, no more."""
 
 import pytest
 
@@ -40,3 +40,14 @@ def test_sequences_that_are_not_normal(m, n):
     # the attempt is one evaluation and a step of a chain: a tenth measured, 3.3 times
     # with a quarter of the blocks that the general kernel has at once
     assert registers < 1.5 * general
+
+
+@pytest.mark.parametrize("count,degree,row", [(3000, 1, 4), (3000, 2, 4), (3000, 4, 5), (1, 1, 4)])
+def test_small_degrees(count, degree, row):
+    # capacity 24 took 2.2, 1.6, 1.4 and 1.9 times the general kernel's time
+    b = br.DeviceBatch([("res",) + synth.random_rect(100 + i % 5, degree, row - 1, degree, row - 1, 20) + ("y",)
+                        for i in range(count)])
+    general, want = evaluation_time(b, "lds")
+    default, got = evaluation_time(b, "auto")
+    assert got == want
+    assert default < 1.25 * general
