@@ -142,7 +142,11 @@ __global__ void k_scan(const ScanTask* tasks, const int4* bmap) {
       }
     }
     for (int d = 1; d < w; d <<= 1) bits = max(bits, __shfl_xor(bits, d));
-    const int fx = cnt ? (int32_t)ceil((log2(norm * (1.0 + 0x1p-40)) + 1e-6) * 1024.0) : 0;
+    // (beyond the double range: the longest coefficient and the count, as on the host)
+    norm *= 1.0 + 0x1p-40;
+    const bool wide = !(norm < HUGE_VAL);
+    int fx = cnt ? (int32_t)ceil((log2(wide ? (double)cnt : norm) + 1e-6) * 1024.0) : 0;
+    if (wide) fx += 1024 * min(bits, 1 << 19);
     if (act && li < 4) T.out[4 * j + li] = li == 0 ? deg : li == 1 ? bits : li == 2 ? cnt : fx;
   }
 }

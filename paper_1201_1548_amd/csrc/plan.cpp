@@ -40,6 +40,11 @@ static int bitlen_abs(const uint32_t* c, int L, bool* nonzero) {
 
 int32_t log2_fx_up(double x) { return (int32_t)std::ceil((std::log2(x) + 1e-6) * 1024.0); }
 
+// log2 of a row's 1-norm in 1/1024 bits from the longest coefficient and the
+// number of non-zero ones, for norms beyond the double range (above 2^1023).  Bounded
+// far above the largest modulus, so that sums of it stay in 32 bits.
+static int32_t wide_norm_fx(int bits, int cnt) { return 1024 * std::min(bits, 1 << 19) + log2_fx_up((double)cnt); }
+
 // Upper bound of |c| as a double: the top 64 magnitude bits plus one unit of
 // the next limb, raised by 2^-52 against the rounding of the conversion.
 static double mag_upper(const uint32_t* c, int L) {
@@ -69,7 +74,8 @@ RowStats scan_host(const uint32_t* limbs, int rows, int ld, int L) {
       }
     }
     // the sum's rounding (at most ld 2^-53 relative) is covered by 2^-40
-    s.set(j, deg, bits, cnt, cnt ? log2_fx_up(norm * (1.0 + 0x1p-40)) : 0);
+    norm *= 1.0 + 0x1p-40;
+    s.set(j, deg, bits, cnt, !cnt ? 0 : std::isfinite(norm) ? log2_fx_up(norm) : wide_norm_fx(bits, cnt));
   }
   return s;
 }
