@@ -61,6 +61,7 @@ void launch_eval_elim_rg(int C, const JobDev* jobs, const int* starts, int nj, i
 // TablesDev::pow_planes for blocks < nb and primes < P on tab's nodes.
 size_t pow_planes_bytes(int nb, int P);
 void launch_pow_planes(TablesDev tab, int nb, int P, int8_t* out, hipStream_t s);
+// The recomputation of launch_eval_elim_rg's queued blocks by at most max_blocks.
 void launch_eval_elim_fb(const JobDev* jobs, const int* starts, int nj, int nblocks, int max_blocks, int max_words,
                          const int* fb_count, const int* fb_queue, TablesDev tab, hipStream_t s);
 // Evaluation + elimination by the Schur algorithm on the displacement

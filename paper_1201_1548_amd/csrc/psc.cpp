@@ -5,8 +5,8 @@
 // psc: the inputs are reduced modulo the prime (k_reduce), every point
 // of the D nodes runs the subresultant recurrence in one lane (k_psc), and
 // each index i is interpolated on those nodes (k_interp_geo on the nodes 2^a,
-// or k_interp on 0..D-1 where the tables of the former would not fit; one
-// block per index).  D is the resultant's point count: sr_i is a minor of the Sylvester
+// with the tables of the one prime, or k_interp on 0..D-1 where these could not
+// be built; one block per index).  D is the resultant's point count: sr_i is a minor of the Sylvester
 // matrix's rows (n - i rows of f, m - i of g), so the degree bound of R bounds
 // it too.  The prime must be one of the library's table primes (the largest
 // below 2^32 / 3), whose tables the kernels index; the kernels see the table
