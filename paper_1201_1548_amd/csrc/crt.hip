@@ -1,5 +1,5 @@
 // (e) the explicit CRT for any prime count whose operands fit in LDS (in
-// practice up to about 700 primes; k_crt_mfma in kernels.hip keeps the
+// practice up to 630 primes; k_crt_mfma in kernels.hip keeps the
 // small counts, whose left operands fit in registers), and its tables.
 //
 // The formula is k_crt_mfma's: with M = prod p_k, y_k the symmetric
