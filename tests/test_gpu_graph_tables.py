@@ -55,43 +55,6 @@ def test_a_replayed_graph_reads_its_own_tables(order, monkeypatch):
         assert r == want[i]
 
 
-def test_tables_that_go_while_other_threads_read_them():
-    # 24 sizes up to 6006 points in growing order, dealt to four threads with a
-    # stream each: every size replaces the tables that the calls in flight read
-    import threading
-
-    import torch
-    batches = [br.DeviceBatch([("res",) + synth.random_rect(171 + k, 1, 5, 1, 250 * (k + 1), 40) + ("y",)])
-               for k in range(24)]
-    torch.cuda.synchronize()
-    got, errors = [None] * 24, []
-
-    def work(t):
-        try:
-            stream = torch.cuda.Stream()
-            for k in range(t, 24, 4):
-                for _ in range(3):
-                    batches[k].run(stream)
-                stream.synchronize()
-                got[k] = batches[k].results()
-        except Exception as e:  # reported by the main thread
-            errors.append(e)
-
-    threads = [threading.Thread(target=work, args=(t,)) for t in range(4)]
-    for t in threads:
-        t.start()
-    for t in threads:
-        t.join()
-    assert not errors
-    try:
-        br.set_eval_kernel("lds")
-        for k, b in enumerate(batches):
-            b.run()
-            assert got[k] == b.results(), k
-    finally:
-        br.set_eval_kernel("auto")
-
-
 def test_outgrown_tables_and_their_graphs():
     # 16 sizes up to 7936 points, each replayed, then all again on the last tables
     batches = [br.DeviceBatch([("res",) + synth.random_rect(71 + k, 1, 5, 1, 256 + 512 * k - 6, 40) + ("y",)])
