@@ -10,13 +10,13 @@ pytestmark = pytest.mark.gpu
 
 
 def evaluation_time(b, kernel):
-    """Milliseconds of the evaluation and elimination launches, best of five calls."""
+    """Milliseconds of the evaluation and elimination launches, best of twenty calls."""
     try:
         br.set_eval_kernel(kernel)
         b.run()
         b.run()
         best = 1e30
-        for _ in range(5):
+        for _ in range(20):
             br.set_timing(True)
             b.run()
             ms, launches = br.kernel_time()

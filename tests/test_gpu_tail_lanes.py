@@ -24,7 +24,7 @@ def evaluation_time(b):
     b.run()
     b.run()
     best = 1e30
-    for _ in range(5):
+    for _ in range(20):
         br.set_timing(True)
         b.run()
         ms, launches = br.kernel_time()
